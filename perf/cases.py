@@ -1,0 +1,355 @@
+"""Timing cases of the matrix-element library: what a Monte Carlo program has it do.
+
+A case is one call, or one short call sequence, of the public binding
+(`QedProcess`, `BatchPlan`, `QedLogM2`) on seeded synthetic points.  `listed`
+holds the benchmark's workloads and, beside them, the sizes such programs meet
+around them; `draw` spreads over the same ranges.  `exact` is the plain
+definition in 64 bits (explicit Dirac matrices, one current per photon subset,
+every helicity separately), independent of the package.
+"""
+import math
+
+import torch
+
+from paper_2511_19456_amd.qedx import BatchPlan, QedLogM2, QedProcess, make_variant
+
+DEV = "cuda"
+
+# FLOPs per point of the cheapest form known of each result: one current per
+# photon subset on either side of the joins (add/mul 1, fma 2).
+FLOPS_PER_POINT = {1: 450, 2: 1170, 3: 2762, 4: 6290, 5: 14074, 6: 31138}   # one configuration, by outgoing photons
+FLOPS_SUM = {1: 2195, 2: 7291, 3: 25003, 4: 84139}                          # all configurations
+FLOPS_GRAD = {1: 8383, 2: 28779, 3: 95127, 4: 330127}                       # with the reverse sweep
+MOST_FLOPS = 87e9                                                           # the listed gradient's
+
+
+def listed():
+    return [
+        # the one-photon workload: electron at rest, photon of energy 1 (launch bound)
+        dict(name="compton_n1_sum", kind="eval", n=1, n_in=1, mode="sum", prec="fp64", rewrite=0, N=65536, rs=0.0),
+        # one small batch of an adaptive sampler, far below a full chip
+        dict(name="sum_n2_small", kind="eval", n=2, n_in=1, mode="sum", prec="fp64", rewrite=0, N=257, rs=6.0),
+        # the headline workload
+        dict(name="sum_n3", kind="eval", n=3, n_in=1, mode="sum", prec="fp64", rewrite=0, N=1 << 20, rs=10.0),
+        # the same process with the distributive rewrite asked for, ragged batch
+        dict(name="sum_n3_rewrite", kind="eval", n=3, n_in=1, mode="sum", prec="fp64", rewrite=1, N=300007, rs=10.0),
+        # the largest helicity sum, ragged batch
+        dict(name="sum_n4", kind="eval", n=4, n_in=1, mode="sum", prec="fp64", rewrite=0, N=99991, rs=15.0),
+        # one configuration per point, both precisions
+        dict(name="pp_n5", kind="eval", n=5, n_in=1, mode="per_point", prec="fp64", rewrite=0, N=1 << 20, rs=20.0),
+        dict(name="pp_n5_fp32c", kind="eval", n=5, n_in=1, mode="per_point", prec="fp32c", rewrite=0, N=1 << 20,
+             rs=20.0),
+        # event generation: phase space, then the matrix element of the most photons
+        dict(name="generate_n6", kind="generate", n=6, n_in=1, mode="per_point", prec="fp64", rewrite=0, N=100003,
+             rs=25.0),
+        # four photons in, one out (the paper's Table I orientation)
+        dict(name="crossed_i4", kind="eval", n=1, n_in=4, mode="per_point", prec="fp64", rewrite=0, N=1 << 20, rs=0.0),
+        # processes n = 1..6 of uneven sizes in one launch
+        dict(name="mixed_n1to6", kind="batch", prec="fp64", rewrite=0, ns="1,2,3,4,5,6",
+             Ns="674790,848655,66385,254509,412008,508915", rss="17.78,7.02,14.41,9.36,18.60,16.93"),
+        # gradients through the phase-space map: the benchmark's, and a training step's through autograd
+        dict(name="grad_n4", kind="grad", n=4, n_in=1, mode="sum", prec="fp64", rewrite=0, N=1 << 18, rs=15.0),
+        dict(name="autograd_n3", kind="autograd", n=3, n_in=1, mode="sum", prec="fp64", rewrite=0, N=20011, rs=10.0),
+    ]
+
+
+def _size(rng, most):
+    """A point count, logarithmically spread over 1..most."""
+    return max(1, min(int(most), int(round(math.exp(rng.uniform(0.0, math.log(most)))))))
+
+
+def draw(rng):
+    kind = rng.choice(["eval"] * 6 + ["crossed", "generate", "batch", "grad", "autograd"])
+    if kind == "batch":
+        k = rng.randint(2, 48)
+        ns = [rng.randint(1, 6) for _ in range(k)]
+        return dict(kind="batch", prec=rng.choice(["fp64", "fp64", "fp32c"]), rewrite=0, ns=",".join(map(str, ns)),
+                    Ns=",".join(str(int(round(10.0 ** rng.uniform(1.0, 4.3)))) for _ in ns),
+                    rss=",".join("%.2f" % rng.uniform(5.0, 30.0) for _ in ns))
+    if kind in ("grad", "autograd"):
+        n = rng.randint(1, 4)
+        most = min(1 << 20, MOST_FLOPS / FLOPS_GRAD[n])
+        return dict(kind=kind, n=n, n_in=1, mode="sum", prec="fp64", rewrite=0, N=_size(rng, most),
+                    rs=round(rng.uniform(3.0 + n, 25.0), 2))
+    if kind == "crossed":
+        n_in = rng.randint(2, 6)
+        mode = "sum" if n_in <= 4 and rng.random() < 0.3 else "per_point"
+        most = min(1 << 20, MOST_FLOPS / 4 / (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n_in])
+        return dict(kind="eval", n=1, n_in=n_in, mode=mode, prec="fp64", rewrite=0, N=_size(rng, most), rs=0.0)
+    mode = "per_point" if kind == "generate" or rng.random() < 0.55 else "sum"
+    n = rng.randint(1, 6) if mode == "per_point" else rng.randint(1, 4)
+    prec, rewrite = "fp64", 0
+    x = rng.random()
+    if x < 0.2 and (mode == "per_point" or n == 3):
+        prec = "fp32c"
+    elif x < 0.4 and n >= 2:
+        rewrite = 1
+    most = min(1 << 20, MOST_FLOPS / 4 / (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n])
+    return dict(kind=kind, n=n, n_in=1, mode=mode, prec=prec, rewrite=rewrite, N=_size(rng, most),
+                rs=round(rng.uniform(3.0 + n, 30.0), 2))
+
+
+# ---------------------------------------------------------------------------
+# inputs
+# ---------------------------------------------------------------------------
+def _uniforms(rows, N, g):
+    u = torch.rand(rows, N, dtype=torch.float64, device=DEV, generator=g)
+    return u.clamp_(min=torch.finfo(torch.float64).tiny)
+
+
+def _incoming(rs):
+    k = (rs * rs - 1.0) / (2.0 * rs)
+    return (math.sqrt(1.0 + k * k), 0.0, 0.0, -k), (k, 0.0, 0.0, k)
+
+
+def _rambo(u, rs):
+    """Kleiss-Stirling-Ellis phase space of one electron (mass 1) and n photons: momenta [n + 3][4] of [N] (differentiable)."""
+    nf = u.shape[0] // 4
+    q = []
+    for j in range(nf):
+        c, ph = 2.0 * u[4 * j] - 1.0, 2.0 * math.pi * u[4 * j + 1]
+        e = -torch.log(u[4 * j + 2] * u[4 * j + 3])
+        st = torch.sqrt(torch.clamp(1.0 - c * c, min=0.0))
+        q.append(torch.stack([e, e * st * torch.cos(ph), e * st * torch.sin(ph), e * c]))
+    Q = sum(q)
+    M = torch.sqrt(Q[0] ** 2 - (Q[1:] ** 2).sum(0))
+    b, x, gam = -Q[1:] / M, rs / M, Q[0] / M
+    a = 1.0 / (1.0 + gam)
+    p = []
+    for v in q:
+        bq = (b * v[1:]).sum(0)
+        p.append(torch.cat([(x * (gam * v[0] + bq))[None], x * (v[1:] + b * (v[0] + a * bq))]))
+    e2, rest = (p[0][0] ** 2).detach(), sum(v[0] for v in p[1:])
+    xi = torch.full_like(e2, math.sqrt(1.0 - 1.0 / (rs * rs)))
+    for _ in range(12):
+        r = torch.sqrt(1.0 + xi * xi * e2)
+        xi = xi - (r + xi * rest.detach() - rs) / (xi * e2 / r + rest.detach())
+    # one more step with the graph attached: the root and its derivative
+    r = torch.sqrt(1.0 + xi * xi * p[0][0] ** 2)
+    xi = xi - (r + xi * rest - rs) / (xi * e2 / torch.sqrt(1.0 + xi * xi * e2) + rest.detach())
+    pin, kin = _incoming(rs)
+    mom = [[torch.full_like(xi, x) for x in pin], [torch.full_like(xi, x) for x in kin]]
+    mom.append([torch.sqrt(1.0 + (xi * p[0][0]) ** 2)] + [xi * p[0][i] for i in (1, 2, 3)])
+    for v in p[1:]:
+        mom.append([xi * v[i] for i in range(4)])
+    return mom
+
+
+def _soa(mom):
+    return torch.stack([x for p in mom for x in p]).contiguous()
+
+
+def _photon(w, u1, u2):
+    c, ph = 2.0 * u1 - 1.0, 2.0 * math.pi * u2
+    s = torch.sqrt(torch.clamp(1.0 - c * c, min=0.0))
+    return [w, w * s * torch.cos(ph), w * s * torch.sin(ph), w * c]
+
+
+def _compton(N, n_in, g):
+    """Electron at rest and n_in photons (one: energy 1 along z) into an electron and a photon isotropic in the c.m. frame
+    (one: in the lab angle)."""
+    u = _uniforms(3 * n_in + 2, N, g)
+    one, nil = torch.ones(N, dtype=torch.float64, device=DEV), torch.zeros(N, dtype=torch.float64, device=DEV)
+    e = [one, nil, nil, nil]
+    if n_in == 1:
+        ks = [[one, nil, nil, one]]
+        out = _photon(1.0 / (1.0 + (1.0 - (2.0 * u[0] - 1.0))), u[0], u[1])
+    else:
+        ks = [_photon(0.5 + 1.5 * u[3 * i], u[3 * i + 1], u[3 * i + 2]) for i in range(n_in)]
+        P = [e[m] + sum(k[m] for k in ks) for m in range(4)]
+        s = P[0] ** 2 - P[1] ** 2 - P[2] ** 2 - P[3] ** 2
+        rs = torch.sqrt(s)
+        w = (s - 1.0) / (2.0 * rs)
+        kc = _photon(w, u[3 * n_in], u[3 * n_in + 1])
+        bt, gam = [P[i] / P[0] for i in (1, 2, 3)], P[0] / rs
+        bk = sum(bt[i] * kc[i + 1] for i in range(3))
+        out = [gam * (w + bk)] + [kc[i + 1] + bt[i] * gam * (gam / (gam + 1.0) * bk + w) for i in range(3)]
+    P = [e[m] + sum(k[m] for k in ks) for m in range(4)]
+    return [e] + ks + [[P[m] - out[m] for m in range(4)], out]
+
+
+def _generator(seed, k=0):
+    return torch.Generator(device=DEV).manual_seed(1000003 * seed + k)
+
+
+def _segments(case):
+    return list(zip([int(x) for x in case["ns"].split(",")], [int(x) for x in case["Ns"].split(",")],
+                    [float(x) for x in case["rss"].split(",")]))
+
+
+def _points(n, N, rs, per_point, n_in, g):
+    """Momenta [4 npart, N] and helicity codes (or None)."""
+    mom = _soa(_compton(N, n_in, g) if rs == 0.0 else _rambo(_uniforms(4 * (n + 1), N, g), rs))
+    hel = torch.randint(0, 1 << (n + n_in + 2), (N,), device=DEV, generator=g, dtype=torch.int32) if per_point else None
+    return mom, hel
+
+
+def _variant(case):
+    return make_variant(rewrite=1) if case["rewrite"] else None
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind == "batch":
+        procs, segs = {}, []
+        for k, (n, N, rs) in enumerate(_segments(case)):
+            if n not in procs:
+                procs[n] = QedProcess(n, "per_point", case["prec"], _variant(case))
+            mom, hel = _points(n, N, rs, True, 1, _generator(seed, k))
+            segs.append((procs[n], mom, hel, torch.empty(N, dtype=torch.float64, device=DEV)))
+        return dict(kind=kind, plan=BatchPlan(segs), outs=[s[3] for s in segs])
+    g = _generator(seed)
+    st = dict(kind=kind, rs=case["rs"], proc=QedProcess(case["n"], case["mode"], case["prec"], _variant(case), case["n_in"]))
+    if kind == "eval":
+        st["mom"], st["hel"] = _points(case["n"], case["N"], case["rs"], case["mode"] == "per_point", case["n_in"], g)
+    else:
+        st["u"] = _uniforms(4 * (case["n"] + 1), case["N"], g)
+        if kind == "generate":
+            st["hel"] = torch.randint(0, 1 << (case["n"] + 3), (case["N"],), device=DEV, generator=g, dtype=torch.int32)
+    return st
+
+
+def run(state):
+    kind = state["kind"]
+    if kind == "batch":
+        state["plan"].launch()
+        return state["outs"]
+    p = state["proc"]
+    if kind == "eval":
+        return p.eval(state["mom"], state["hel"])
+    if kind == "generate":
+        mom = p.rambo(state["u"], state["rs"])
+        return mom, p.eval(mom, state["hel"])
+    if kind == "grad":
+        return p.eval_grad(state["u"], state["rs"])
+    x = state["u"].detach().requires_grad_()
+    y = QedLogM2.apply(x, p, state["rs"])
+    (gx,) = torch.autograd.grad(y.sum(), x)
+    return y.detach(), gx
+
+
+def work(case):
+    if case["kind"] == "batch":
+        segs = _segments(case)
+        return {"bytes": sum(N * (32 * (n + 3) + 12) for n, N, _ in segs),
+                "flops": sum(N * FLOPS_PER_POINT[n] for n, N, _ in segs)}
+    n, N = case["n"] + case["n_in"] - 1, case["N"]
+    if case["kind"] in ("grad", "autograd"):
+        return {"bytes": N * (2 * 32 * (n + 1) + 8), "flops": N * FLOPS_GRAD[n]}
+    per_point = case["mode"] == "per_point"
+    b = 32 * (n + 3) + 8 + (4 if per_point else 0)
+    if case["kind"] == "generate":
+        b += 32 * (n + 1)
+    return {"bytes": N * b, "flops": N * (FLOPS_PER_POINT if per_point else FLOPS_SUM)[n]}
+
+
+# ---------------------------------------------------------------------------
+# plain definition in 64 bits
+# ---------------------------------------------------------------------------
+def _sigma(v, x):
+    """(v . sigma) x for a real 3-vector and a 2-spinor."""
+    c = torch.complex(v[0], v[1])
+    return v[2] * x[0] + c.conj() * x[1], c * x[0] - v[2] * x[1]
+
+
+def _eps(k, lam):
+    """Linear polarisation lam (0 x, 1 y; a tensor of the points' shape) in the theta/phi basis of k."""
+    kt2 = k[1] ** 2 + k[2] ** 2
+    flat = kt2 == 0.0
+    kt = torch.sqrt(torch.where(flat, torch.ones_like(kt2), kt2))
+    kk = torch.sqrt(torch.where(flat, torch.ones_like(kt2), kt2 + k[3] ** 2))
+    cf, sf = torch.where(flat, torch.ones_like(kt), k[1] / kt), torch.where(flat, torch.zeros_like(kt), k[2] / kt)
+    ct = torch.where(flat, torch.sign(k[3]), k[3] / kk)
+    st = torch.where(flat, torch.zeros_like(kt), kt / kk)
+    y = lam == 1
+    return (torch.where(y, -sf, ct * cf), torch.where(y, cf, ct * sf), torch.where(y, torch.zeros_like(st), -st))
+
+
+def _spinor(p, spin):
+    """Dirac-basis u(p, s): (sqrt(E + 1) chi, sigma.p chi / sqrt(E + 1))."""
+    r = torch.sqrt(p[0] + 1.0)
+    up = spin == 0
+    one, nil = torch.ones_like(r), torch.zeros_like(r)
+    chi = [torch.where(up, one, nil) + 0j, torch.where(up, nil, one) + 0j]
+    s = _sigma(p[1:], chi)
+    return [r * chi[0], r * chi[1], s[0] / r, s[1] / r]
+
+
+def _amp2(mom, n_in, hel):
+    """|A_h|^2 for momenta mom[particle][4] and helicity codes, all broadcast to one shape."""
+    npart = len(mom)
+    P, eout = npart - 2, n_in + 1
+    ph = [i for i in range(npart) if i not in (0, eout)]
+    sg = [1.0 if i < eout else -1.0 for i in ph]
+    bit = [(hel >> i) & 1 for i in range(npart)]
+    eps = [_eps(mom[i], bit[i]) for i in ph]
+    K, J = {0: None}, {0: _spinor(mom[0], bit[0])}
+    full = (1 << P) - 1
+    for S in sorted(range(1, full + 1), key=lambda m: bin(m).count("1")):
+        cur = None
+        for a in range(P):
+            if not (S >> a) & 1:
+                continue
+            x = J[S & ~(1 << a)]
+            lo, hi = _sigma(eps[a], x[2:]), _sigma(eps[a], x[:2])
+            t = [-lo[0], -lo[1], hi[0], hi[1]]
+            cur = t if cur is None else [c + d for c, d in zip(cur, t)]
+        if S == full:
+            ub = [z.conj() for z in _spinor(mom[eout], bit[eout])]
+            A = ub[0] * cur[0] + ub[1] * cur[1] - ub[2] * cur[2] - ub[3] * cur[3]
+            return A.real ** 2 + A.imag ** 2
+        a = (S & -S).bit_length() - 1
+        k = [sg[a] * c for c in mom[ph[a]]]
+        K[S] = k if S == 1 << a else [c + d for c, d in zip(K[S & ~(1 << a)], k)]
+        k, p = K[S], mom[0]
+        D = 2.0 * (p[0] * k[0] - p[1] * k[1] - p[2] * k[2] - p[3] * k[3]) + k[0] ** 2 - k[1] ** 2 - k[2] ** 2 - k[3] ** 2
+        q = [(p[i] + k[i]) / D for i in range(4)]
+        up, dn = _sigma(q[1:], cur[:2]), _sigma(q[1:], cur[2:])
+        m = 1.0 / D
+        J[S] = [(q[0] + m) * cur[0] - dn[0], (q[0] + m) * cur[1] - dn[1],
+                up[0] + (m - q[0]) * cur[2], up[1] + (m - q[0]) * cur[3]]
+
+
+def _m2(mom, n_in, hel):
+    """|M|^2 [N] of momenta [particle][4] of [N]: of codes hel, or summed over all of them."""
+    if hel is not None:
+        return _amp2(mom, n_in, hel.to(torch.int64))
+    h = torch.arange(1 << len(mom), device=DEV)[:, None]
+    return _amp2([[c[None, :] for c in p] for p in mom], n_in, h.expand(-1, mom[0][0].shape[0])).sum(0)
+
+
+def _exact_m2(mom, n_in, hel):
+    npart, N = mom.shape[0] // 4, mom.shape[1]
+    step = max(1, (1 << 22) >> (0 if hel is not None else npart))
+    out = torch.empty(N, dtype=torch.float64, device=DEV)
+    for i in range(0, N, step):
+        m = mom[:, i:i + step]
+        out[i:i + step] = _m2([[m[4 * p + c] for c in range(4)] for p in range(npart)], n_in,
+                              None if hel is None else hel[i:i + step])
+    return out
+
+
+def exact(case, seed):
+    if case["kind"] == "batch":
+        outs = []
+        for k, (n, N, rs) in enumerate(_segments(case)):
+            mom, hel = _points(n, N, rs, True, 1, _generator(seed, k))
+            outs.append(_exact_m2(mom, 1, hel))
+        return outs
+    g = _generator(seed)
+    if case["kind"] == "eval":
+        mom, hel = _points(case["n"], case["N"], case["rs"], case["mode"] == "per_point", case["n_in"], g)
+        return _exact_m2(mom, case["n_in"], hel)
+    u = _uniforms(4 * (case["n"] + 1), case["N"], g)
+    if case["kind"] == "generate":
+        hel = torch.randint(0, 1 << (case["n"] + 3), (case["N"],), device=DEV, generator=g, dtype=torch.int32)
+        mom = _soa(_rambo(u, case["rs"]))
+        return mom, _exact_m2(mom, 1, hel)
+    val, grad = torch.empty(case["N"], dtype=torch.float64, device=DEV), torch.empty_like(u)
+    step = (1 << 20) >> (case["n"] + 3)
+    for i in range(0, case["N"], step):
+        x = u[:, i:i + step].clone().requires_grad_()
+        y = torch.log(_m2(_rambo(x, case["rs"]), 1, None))
+        (gx,) = torch.autograd.grad(y.sum(), x)
+        val[i:i + step], grad[:, i:i + step] = y.detach(), gx
+    return val, grad
