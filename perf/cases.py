@@ -15,12 +15,12 @@ from paper_2511_19456_amd.qedx import BatchPlan, QedLogM2, QedProcess, make_vari
 
 DEV = "cuda"
 
-# FLOPs per point of the cheapest form known of each result: one current per
-# photon subset on either side of the joins (add/mul 1, fma 2).
+# FLOPs per point of the cheapest form known of each result (add/mul 1, fma 2): one current per photon subset and side,
+# and for sums over all configurations one spin of the incoming electron (flipping both electron spins conjugates A).
 FLOPS_PER_POINT = {1: 450, 2: 1170, 3: 2762, 4: 6290, 5: 14074, 6: 31138}   # one configuration, by outgoing photons
-FLOPS_SUM = {1: 2195, 2: 7291, 3: 25003, 4: 84139}                          # all configurations
-FLOPS_GRAD = {1: 8383, 2: 28779, 3: 95127, 4: 330127}                       # with the reverse sweep
-MOST_FLOPS = 87e9                                                           # the listed gradient's
+FLOPS_SUM = {1: 1523, 2: 4315, 3: 13467, 4: 44715}                          # all configurations
+FLOPS_GRAD = {1: 5703, 2: 15969, 3: 49263, 4: 161637}                       # with the reverse sweep
+MOST_FLOPS = 42e9                                                           # the listed gradient's
 
 
 def listed():
@@ -74,7 +74,7 @@ def draw(rng):
     if kind == "crossed":
         n_in = rng.randint(2, 6)
         mode = "sum" if n_in <= 4 and rng.random() < 0.3 else "per_point"
-        most = min(1 << 20, MOST_FLOPS / 4 / (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n_in])
+        most = min(1 << 20, MOST_FLOPS / 2 / (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n_in])
         return dict(kind="eval", n=1, n_in=n_in, mode=mode, prec="fp64", rewrite=0, N=_size(rng, most), rs=0.0)
     mode = "per_point" if kind == "generate" or rng.random() < 0.55 else "sum"
     n = rng.randint(1, 6) if mode == "per_point" else rng.randint(1, 4)
@@ -84,7 +84,7 @@ def draw(rng):
         prec = "fp32c"
     elif x < 0.4 and n >= 2:
         rewrite = 1
-    most = min(1 << 20, MOST_FLOPS / 4 / (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n])
+    most = min(1 << 20, MOST_FLOPS / 2 / (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n])
     return dict(kind=kind, n=n, n_in=1, mode=mode, prec=prec, rewrite=rewrite, N=_size(rng, most),
                 rs=round(rng.uniform(3.0 + n, 30.0), 2))
 
