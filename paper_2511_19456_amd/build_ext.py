@@ -1,8 +1,8 @@
 """Build the qedx native library and prebuild its kernel cache.
 
 Steps
-1. Embed the device headers (qedx_device.h, qedx_rambo.h) as a raw string
-   literal so generated kernels are self-contained translation units.
+1. Embed the device headers (qedx_device.h, qedx_rambo.h; qedx_subset.h) as raw
+   string literals so generated kernels are self-contained translation units.
 2. Compile the host library libqedx.so (graph builder, reducer, emitter,
    runtime) with the host C++ compiler against the HIP runtime.
 3. Emit and compile (hipcc --genco, gfx950) the kernels of the default process
@@ -28,26 +28,28 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libqedx.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
-HOST_SOURCES = ["qedx_dag.cpp", "qedx_emit.cpp", "qedx_kernels.cpp", "qedx_runtime.cpp", "qedx_batch.cpp",
+HOST_SOURCES = ["qedx_dag.cpp", "qedx_emit.cpp", "qedx_pair.cpp", "qedx_kernels.cpp", "qedx_runtime.cpp", "qedx_batch.cpp",
                 "qedx_hosttools.cpp"]
 # measurement tool kept out of the evaluation library (include/qedx_probe.h)
 PROBE_SOURCES = ["qedx_probe.cpp"]
 PROBE_LIB = os.path.join(PKG, "libqedx_probe.so")
 DEVICE_HEADERS = ["qedx_device.h", "qedx_rambo.h"]
+SUBSET_HEADERS = ["qedx_subset.h"]
 
 
 def embed_headers() -> None:
-    parts = []
-    for h in DEVICE_HEADERS:
-        txt = open(os.path.join(CSRC, h)).read().replace("#pragma once\n", "")
-        parts.append(txt)
-    body = "\n".join(parts)
-    assert ")QEDXHDR\"" not in body
-    out = 'R"QEDXHDR(' + body + ')QEDXHDR"\n'
-    path = os.path.join(CSRC, "qedx_device_embed.inc")
-    if not os.path.exists(path) or open(path).read() != out:
-        with open(path, "w") as f:
-            f.write(out)
+    for headers, name in ((DEVICE_HEADERS, "qedx_device_embed.inc"), (SUBSET_HEADERS, "qedx_subset_embed.inc")):
+        parts = []
+        for h in headers:
+            txt = open(os.path.join(CSRC, h)).read().replace("#pragma once\n", "")
+            parts.append(txt)
+        body = "\n".join(parts)
+        assert ")QEDXHDR\"" not in body
+        out = 'R"QEDXHDR(' + body + ')QEDXHDR"\n'
+        path = os.path.join(CSRC, name)
+        if not os.path.exists(path) or open(path).read() != out:
+            with open(path, "w") as f:
+                f.write(out)
 
 
 def _compile_objects(sources, verbose):

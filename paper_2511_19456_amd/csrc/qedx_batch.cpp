@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "qedx_internal.hpp"
+#include "qedx_pair.hpp"
 
 using namespace qedx;
 using qedx_rt::fail;
@@ -39,6 +40,7 @@ struct DevSeg {  // mirrored by qedx_seg in the generated module
   long long tile0;
   int proc;
   int shift;       // log2 of the process body's lanes per point
+  int shift64;     // ... of its body in the FP32C fix-up pass
   long long list0; // FP32C fix-up: the segment's region of the point list
 };
 
@@ -73,11 +75,21 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   // Bodies with the one-photon current cache (FP64 per point, 5..7 photons)
   // run 2 or 4 lanes per point and keep the cache in their wave's region of
   // qx_cache_mem.
-  std::vector<char> pol(procs.size(), 0), cache(procs.size(), 0), cache64(procs.size(), 0);
+  // FP64 processes without an explicit kernel shape take the pair bodies (two
+  // lanes per point).
+  std::vector<char> pol(procs.size(), 0), cache(procs.size(), 0), cache64(procs.size(), 0), pair(procs.size(), 0);
+  os << subset_header_text() << "\n";
   int pol_npart = 0, cache_w = 0, cache_w64 = 0;
   for (size_t i = 0; i < procs.size(); ++i) {
     Dag d = graph_for(procs[i].first, procs[i].second, nullptr, nullptr);
     EmitStats st;
+    const Process& pr = procs[i].first;
+    pair[i] = pair_kernel(pr, procs[i].second);
+    if (pair[i] && !fix) {
+      cache_w = std::max(cache_w, pair_lds_doubles(pr));
+      os << emit_pair_body(pr, "qedx_body_" + std::to_string(i), &st) << "\n";
+      continue;
+    }
     const int cw = body_cache_doubles(d, procs[i].second);
     cache[i] = cw > 0;
     cache_w = std::max(cache_w, cw);
@@ -88,6 +100,11 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
       Variant v64 = procs[i].second;
       v64.prec = PREC_F64;
       v64.fixup = 0;
+      if (pair[i]) {
+        cache_w64 = std::max(cache_w64, pair_lds_doubles(pr));
+        os << emit_pair_body(pr, "qedx_body64_" + std::to_string(i), &st) << "\n";
+        continue;
+      }
       const int cw64 = body_cache_doubles(d, v64);
       cache64[i] = cw64 > 0;
       cache_w64 = std::max(cache_w64, cw64);
@@ -95,7 +112,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
     }
   }
   os << "struct qedx_seg { const double* mom; const unsigned* hel; double* out; long long N; long long tile0; "
-        "int proc; int shift; long long list0; };\n";
+        "int proc; int shift; int shift64; long long list0; };\n";
   os << "extern \"C\" __global__ void __launch_bounds__(256)\n"
         "qedx_batch(const qedx_seg* __restrict__ segs, int nseg, long long ntiles, int chunk, "
         "unsigned* __restrict__ counter"
@@ -105,7 +122,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   for (size_t i = 0; i < procs.size(); ++i)
     if (pol[i]) PT = pol_lds_type(procs[i].second);
   if (pol_npart > 0) os << "  __shared__ " << PT << " qx_pol_mem[" << 3 * pol_npart * 256 << "];\n";
-  if (cache_w > 0) os << "  __shared__ double qx_cache_mem[" << 4 * cache_w << "];\n";
+  if (cache_w > 0) os << "  __shared__ double2 qx_cache_mem[" << 2 * cache_w << "];\n";
   os << "  const int lane = threadIdx.x & 63;\n";
   os << "  while (true) {\n";
   os << "    unsigned t = 0;\n";
@@ -127,10 +144,14 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   if (fix) os << "      int ff = 0;\n";
   os << "      switch (sg.proc) {\n";
   for (size_t i = 0; i < procs.size(); ++i)
-    os << "        case " << i << ": r = qedx_body_" << i << "(sg.mom, sg.N, ptc, hrt"
-       << (cache[i] ? ", qx_cache_mem + (threadIdx.x >> 6) * " + std::to_string(cache_w) + ", lp, sub"
-                    : pol[i] ? ", qx_pol_mem" : "")
-       << (fix ? ", ff, fix_kappa" : "") << "); break;\n";
+    if (pair[i] && !fix)
+      os << "        case " << i << ": r = qedx_body_" << i << "(sg.mom, sg.hel, sg.N, ptc, "
+         << (cache_w ? "(double*)qx_cache_mem + (threadIdx.x >> 6) * " + std::to_string(cache_w) : "nullptr") << "); break;\n";
+    else
+      os << "        case " << i << ": r = qedx_body_" << i << "(sg.mom, sg.N, ptc, hrt"
+         << (cache[i] ? ", (double*)qx_cache_mem + (threadIdx.x >> 6) * " + std::to_string(cache_w) + ", lp, sub"
+                      : pol[i] ? ", qx_pol_mem" : "")
+         << (fix ? ", ff, fix_kappa" : "") << "); break;\n";
   os << "        default: break;\n      }\n";
   os << "      if (pt < sg.N && sub == 0u) sg.out[pt] = r;\n";
   if (fix) {
@@ -158,24 +179,28 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
     os << "extern \"C\" __global__ void __launch_bounds__(256)\n"
           "qedx_batch_fix(const qedx_seg* __restrict__ segs, int nseg, const unsigned* __restrict__ fix_cnt, "
           "const unsigned* __restrict__ fix_list)\n{\n";
-    if (cache_w64 > 0) os << "  __shared__ double qx_fc[" << 4 * cache_w64 << "];\n";
+    if (cache_w64 > 0) os << "  __shared__ double2 qx_fc[" << 2 * cache_w64 << "];\n";
     os << "  const int lane = threadIdx.x & 63;\n"
           "  const long long wave = (long long)blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = (long long)gridDim.x * 4;\n"
           "  for (int s = 0; s < nseg; ++s) {\n"
           "    const qedx_seg sg = segs[s];\n"
           "    const long long cnt = (long long)fix_cnt[s];\n"
-          "    const int lp = lane >> sg.shift;\n"
-          "    const unsigned sub = (unsigned)(lane & ((1 << sg.shift) - 1));\n"
-          "    const long long ppw = 64LL >> sg.shift;\n"
+          "    const int lp = lane >> sg.shift64;\n"
+          "    const unsigned sub = (unsigned)(lane & ((1 << sg.shift64) - 1));\n"
+          "    const long long ppw = 64LL >> sg.shift64;\n"
           "    for (long long j0 = wave * ppw; j0 < cnt; j0 += nwaves * ppw) {\n"
           "      const long long j = j0 + lp;\n"
           "      const long long pt = (long long)fix_list[sg.list0 + (j < cnt ? j : cnt - 1)];\n"
           "      double r = 0.0;\n"
           "      switch (sg.proc) {\n";
     for (size_t i = 0; i < procs.size(); ++i)
-      os << "        case " << i << ": r = qedx_body64_" << i << "(sg.mom, sg.N, pt, sg.hel[pt]"
-         << (cache64[i] ? ", qx_fc + (threadIdx.x >> 6) * " + std::to_string(cache_w64) + ", lp, sub" : "")
-         << "); break;\n";
+      if (pair[i])
+        os << "        case " << i << ": r = qedx_body64_" << i << "(sg.mom, sg.hel, sg.N, pt, "
+           << (cache_w64 ? "(double*)qx_fc + (threadIdx.x >> 6) * " + std::to_string(cache_w64) : "nullptr") << "); break;\n";
+      else
+        os << "        case " << i << ": r = qedx_body64_" << i << "(sg.mom, sg.N, pt, sg.hel[pt]"
+           << (cache64[i] ? ", (double*)qx_fc + (threadIdx.x >> 6) * " + std::to_string(cache_w64) + ", lp, sub" : "")
+           << "); break;\n";
     os << "        default: break;\n      }\n"
           "      if (j < cnt && sub == 0u) sg.out[pt] = r;\n    }\n  }\n}\n";
   }
@@ -228,7 +253,7 @@ struct qed_batch_plan {
   long long ntiles = 0;
   int chunk = 1;
   int grid = 0;  // workgroups of 256 threads
-  std::vector<int> shift;  // per distinct process: log2 of its body's lanes per point
+  std::vector<int> shift, shift64;  // per distinct process: log2 of its bodies' lanes per point
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -289,6 +314,7 @@ static qed_status layout_tiles(qed_batch_plan* b, const qed_segment* segs, const
     d.tile0 = t0;
     d.proc = proc_of[i];
     d.shift = b->shift[proc_of[i]];
+    d.shift64 = b->shift64[proc_of[i]];
     d.list0 = l0;
     l0 += segs[i].N;
     b->host.push_back(d);
@@ -326,7 +352,8 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
     if (s.N >= (1LL << 31)) return fail(QED_ERR_INVALID_ARG, "segment too large");
     // processes with the same kernel shape share one body in the module
     auto same = [&](const qed_process* q) {
-      return variant_tag(q->var, q->proc.n_out, q->proc.n_in) == variant_tag(s.proc->var, s.proc->proc.n_out, s.proc->proc.n_in);
+      return q->var.subset == s.proc->var.subset &&
+             variant_tag(q->var, q->proc.n_out, q->proc.n_in) == variant_tag(s.proc->var, s.proc->proc.n_out, s.proc->proc.n_in);
     };
     auto it = std::find_if(procs.begin(), procs.end(), same);
     if (it == procs.end()) {
@@ -339,7 +366,11 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   }
   auto b = std::make_unique<qed_batch_plan>();
   b->nseg = nseg;
-  for (auto* p : procs) b->shift.push_back(__builtin_ctz(cache_lanes(p->var)));
+  for (auto* p : procs) {
+    const bool pair = pair_kernel(p->proc, p->var);
+    b->shift.push_back(pair && p->prec == QED_FP64 ? 1 : __builtin_ctz(cache_lanes(p->var)));
+    b->shift64.push_back(pair ? 1 : __builtin_ctz(cache_lanes(p->var)));
+  }
   // module (cached like every generated unit)
   std::string src;
   std::vector<std::pair<Process, Variant>> pv;

@@ -7,6 +7,7 @@
 // joins by photon partition so that the currents of one partition are live
 // together; LLVM allocates registers for the resulting basic block.
 #include "qedx_emit.hpp"
+#include "qedx_pair.hpp"
 
 #include <algorithm>
 #include <array>
@@ -21,6 +22,15 @@ namespace qedx {
 static const char* kDeviceHeaderText =
 #include "qedx_device_embed.inc"
     ;
+
+static const char* kSubsetHeaderText =
+#include "qedx_subset_embed.inc"
+    ;
+
+const std::string& subset_header_text() {
+  static const std::string s(kSubsetHeaderText);
+  return s;
+}
 
 const std::string& device_header_text() {
   static const std::string s(kDeviceHeaderText);
@@ -1812,11 +1822,15 @@ std::string emit_eval_kernel(const Dag& d, const Variant& v, const std::string& 
     v64.min_waves = 0;
     EmitStats st64;
     std::ostringstream fx;
-    fx << emit_body_function(d, v64, kname + "_b64", &st64) << "\n";
-    // with the one-photon current cache the FP64 body takes CL lanes per
-    // point and its wave's LDS region
-    const int CL = cache_lanes(v64);
-    const int W = body_cache_doubles(d, v64);
+    const bool pair = pair_kernel(d.proc, v64);
+    if (pair)
+      fx << subset_header_text() << "\n" << emit_pair_body(d.proc, kname + "_b64", &st64) << "\n";
+    else
+      fx << emit_body_function(d, v64, kname + "_b64", &st64) << "\n";
+    // the pair body, and the FP64 body with the one-photon current cache,
+    // take CL lanes per point and their wave's LDS region
+    const int CL = pair ? 2 : cache_lanes(v64);
+    const int W = pair ? pair_lds_doubles(d.proc) : body_cache_doubles(d, v64);
     // Each workgroup of 256 lanes owns kFixRange consecutive points: it scans
     // their results for the negative marks, compacts the marked offsets in
     // LDS (one LDS atomic per wave: ballot, then each marked lane's rank
@@ -1825,8 +1839,8 @@ std::string emit_eval_kernel(const Dag& d, const Variant& v, const std::string& 
     fx << "extern \"C\" __global__ void __launch_bounds__(256)\n"
        << kname << "_fix(const double* __restrict__ mom, const unsigned* __restrict__ hel, long long N, "
        << "double* __restrict__ out)\n{\n"
-       << (W ? "  __shared__ double qx_fc[" + std::to_string(4 * W) + "];\n" : std::string())
-       << "  __shared__ unsigned fx_list[" << kFixRange << "];\n"
+       << (W ? "  __shared__ double2 qx_fc[" + std::to_string(2 * W) + "];\n" : std::string())
+       << "  __shared__ unsigned short fx_list[" << kFixRange << "];\n"
        << "  __shared__ unsigned fx_cnt;\n"
        << "  if (threadIdx.x == 0) fx_cnt = 0u;\n"
        << "  __syncthreads();\n"
@@ -1841,7 +1855,7 @@ std::string emit_eval_kernel(const Dag& d, const Variant& v, const std::string& 
        << "      unsigned b_ = 0u;\n"
        << "      if (ln_ == ld_) b_ = atomicAdd(&fx_cnt, (unsigned)__popcll(fm_));\n"
        << "      b_ = __shfl(b_, (int)ld_);\n"
-       << "      if (f_) fx_list[b_ + (unsigned)__popcll(fm_ & ((1ull << ln_) - 1ull))] = i;\n"
+       << "      if (f_) fx_list[b_ + (unsigned)__popcll(fm_ & ((1ull << ln_) - 1ull))] = (unsigned short)i;\n"
        << "    }\n"
        << "  }\n"
        << "  __syncthreads();\n"
@@ -1858,8 +1872,10 @@ std::string emit_eval_kernel(const Dag& d, const Variant& v, const std::string& 
          << "  for (unsigned j0 = 0; j0 < cnt; j0 += " << 256 / CL << "u) {\n"
          << "    const unsigned j = j0 + (threadIdx.x >> " << sh << ");\n"
          << "    const long long pt = base + (long long)fx_list[j < cnt ? j : cnt - 1u];\n"
-         << "    const double r = " << kname << "_b64(mom, N, pt, hel[pt], qx_fc + (threadIdx.x >> 6) * " << W
-         << ", (int)((threadIdx.x & 63u) >> " << sh << "), sub);\n"
+         << "    const double r = " << kname << "_b64(mom, "
+         << (pair ? "hel, N, pt, " : "N, pt, hel[pt], ")
+         << (W ? "(double*)qx_fc + (threadIdx.x >> 6) * " + std::to_string(W) : std::string("nullptr"))
+         << (pair ? std::string() : ", (int)((threadIdx.x & 63u) >> " + std::to_string(sh) + "), sub") << ");\n"
          << "    if (j < cnt && sub == 0u) out[pt] = r;\n"
          << "  }\n}\n";
     }

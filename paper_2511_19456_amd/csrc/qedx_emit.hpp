@@ -32,6 +32,8 @@ struct Variant {
   int partial = 0;      // 1: unsplit graph after partial_steps single reductions only
   int partial_steps = 0;
   uint32_t partial_seed = 0;
+  int subset = 0;       // 1: no kernel shape was asked for, so FP64 evaluation takes one current per photon
+                        // subset whatever the graph form; the fields above then shape FP32C and the gradient only
   int fixup = 0;        // 1: FP32C per-point kernel flags ill-conditioned points for an FP64 pass
 };
 
@@ -43,7 +45,7 @@ inline int cache_lanes(const Variant& v) { return (v.order & 512) ? 4 : (v.order
 inline int lanes_per_point(const Variant& v) { return (1 << __builtin_popcount(v.lane_mask)) * cache_lanes(v); }
 
 // Points scanned by one workgroup of the FP64 fix-up pass.
-constexpr int kFixRange = 1024;
+constexpr int kFixRange = 1024;  // offsets fit 16 bits
 
 struct EmitStats {
   double flops_per_point = 0;   // algorithmic FLOPs per phase-space point
@@ -137,5 +139,7 @@ std::string pol_lds_type(const Variant& v);
 
 // The device header text (inlined into every generated unit).
 const std::string& device_header_text();
+// ... and what the subset-current kernels add to it.
+const std::string& subset_header_text();
 
 }  // namespace qedx

@@ -1,0 +1,55 @@
+// qedx_pair.hpp -- FP64 kernels for one configuration per point, two lanes
+// per point.
+//
+// Lane 0 of a point builds the currents of the photon subsets from e-_in,
+// lane 1 those from e-_out, one current per subset (the sum over the photon
+// orderings is taken before the next vertex).  Written as a column through
+// the antiunitary map that turns the row ubar(p', s) into the column u(p', 1 - s),
+// the e-_out side obeys the same vertex and propagator with Q = p' - K in
+// place of Q = p + K, so both lanes run one instruction stream on their own
+// electron momentum, spin and sign of K.  The join takes half of the photon
+// partitions on each lane, which hands its partner one current per pair of
+// partitions (DPP lane swap).
+//
+// Bound by FP64 vector instructions: 1.1 (4 photons) to 12.3 (7 photons)
+// thousand per lane, 0.85-0.9 of them FP64 arithmetic, against 3626 to 283306
+// FLOPs of the graph that keeps the orderings apart.  Two lanes, because one
+// lane's registers hold one side's currents (P = 6: 15 of 8 doubles) and not
+// both.  They stay in registers up to 6 photons (vector and accumulation
+// registers, one wave per SIMD): kept in LDS instead, 8 of the 15 took 408 us
+// where the registers take 361 (2^20 points, P = 6).  One wave per SIMD hides
+// no load, so P = 5, 6 loop over the points and load the next ones' momenta
+// while they work (P = 6 without: 445 us; P = 5: 169 against 181 us); P <= 4
+// fits 2 to 8 waves per SIMD and is faster in one pass (P = 4: 75 against 88
+// us).  P = 7 has no registers left for that: its three-photon currents with
+// the last photon go to LDS, the others are built where the join needs them.
+// Against one product per ordering (2^20 points): P = 5 418 -> 169 us, P = 6
+// 1421 -> 361 us; P = 7, 100003 points with their phase space, 874 -> 143 us;
+// the mixed n = 1..6 batch of 2.77 M points 4.62 -> 1.08 ms.
+#pragma once
+
+#include <string>
+
+#include "qedx_dag.hpp"
+#include "qedx_emit.hpp"
+
+namespace qedx {
+
+// Whether (process, variant) is evaluated by the pair kernels.
+inline bool pair_kernel(const Process& pr, const Variant& v) { return v.subset && v.mode == HEL_PER_POINT; }
+
+// Device function text
+//   static __device__ double <fname>(const double* mom, const unsigned* hel, long long N, long long pt, double* lds)
+// for lanes 2i, 2i + 1 of a wave working on the same point; both return the
+// point's |A|^2.  lds: the wave's region of pair_lds_doubles() doubles, 16-byte aligned.
+std::string emit_pair_body(const Process& pr, const std::string& fname, EmitStats* st);
+int pair_lds_doubles(const Process& pr);
+// Whether the eval kernel is launched with one workgroup per compute unit and loops over the points.
+bool pair_persistent(const Process& pr);
+// Waves per SIMD the body's registers and LDS are laid out for.
+int pair_waves(const Process& pr);
+
+// The eval kernel around it: extern "C" __global__ void <kname>(mom, hel, N, out).
+std::string emit_pair_kernel(const Process& pr, const Variant& v, const std::string& kname, EmitStats* st);
+
+}  // namespace qedx

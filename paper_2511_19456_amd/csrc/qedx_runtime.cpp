@@ -33,6 +33,7 @@
 #include "qedx_internal.hpp"
 #include "qedx_scratch.hpp"
 #include "qedx_kernels.hpp"
+#include "qedx_pair.hpp"
 
 extern char** environ;
 
@@ -397,6 +398,8 @@ static qed_status make_variant_shape(int n, int nin, qed_hel_mode mode, qed_prec
       return fail(QED_ERR_INVALID_ARG, "lane_bits/loop_bits apply to SUM mode only");
     }
   }
+  v.subset = !qv || qv->use_defaults ||
+             !(qv->lane_bits || qv->loop_bits || qv->block || qv->split || qv->min_waves || qv->order || qv->partial);
   // FP32C with one photon on the e-_in side of every join: the join's
   // propagator goes onto that side, where it follows the first vertex and is
   // evaluated in FP64 with it (the product next to the external electron can
@@ -448,7 +451,10 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
     info.nodes_reduced = (int64_t)d.nodes.size();
     auto t0 = std::chrono::steady_clock::now();
     EmitStats st;
-    src = emit_eval_kernel(d, v, eval_kernel_name(n, nin, mode, prec, v), &st);
+    const bool pair = prec == QED_FP64 && pair_kernel(proc, v);
+    src = pair ? emit_pair_kernel(proc, v, eval_kernel_name(n, nin, mode, prec, v), &st)
+               : emit_eval_kernel(d, v, eval_kernel_name(n, nin, mode, prec, v), &st);
+    info.lanes_per_point = pair ? 2 : lanes_per_point(v);
     info.create_ms_emit = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     info.n_V = st.n_V;
     info.n_S1 = st.n_S1;
@@ -461,7 +467,6 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
   info.n = n;
   info.mode = mode;
   info.precision = prec;
-  info.lanes_per_point = lanes_per_point(v);
   info.block = v.block;
   std::string tag = variant_tag(v, n, nin);
   snprintf(info.kernel_tag, sizeof info.kernel_tag, "%s", tag.c_str());
@@ -556,6 +561,12 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   auto t0 = std::chrono::steady_clock::now();
   HIPCHK(hipModuleLoadData(&p->mod, co.data()));
   HIPCHK(hipModuleGetFunction(&p->f_eval, p->mod, p->info.kernel_name));
+  if (prec == QED_FP64 && pair_kernel(p->proc, p->var) && pair_persistent(p->proc)) {
+    int dev = 0, ncu = 256;
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    p->max_groups = ncu;
+  }
   if (p->var.fixup) {
     std::string fx = std::string(p->info.kernel_name) + "_fix";
     HIPCHK(hipModuleGetFunction(&p->f_fix, p->mod, fx.c_str()));
@@ -644,7 +655,9 @@ extern "C" qed_status qed_eval(const qed_process* p, const double* momenta, cons
   long long n = (long long)N;
   if (!p->f_fix) {
     void* args[] = {(void*)&momenta, (void*)&hel, (void*)&n, (void*)&out};
-    return launch(p->f_eval, N * (int64_t)p->lanes, p->var.block, stream, args);
+    int64_t threads = N * (int64_t)p->lanes;
+    if (p->max_groups) threads = std::min(threads, p->max_groups * (int64_t)p->var.block);
+    return launch(p->f_eval, threads, p->var.block, stream, args);
   }
   // FP32C pass, which marks the points it cannot resolve with a negative
   // value in `out`, then the FP64 pass over those marks (one workgroup per

@@ -1,0 +1,50 @@
+// qedx_subset.h -- building blocks of the kernels that take one current per
+// photon subset, beside those of qedx_device.h.
+#pragma once
+
+namespace qx {
+
+// acc += eps-slash J, 8 x 3 FMAs
+template <class T> QEDX_HD void vL_add(sp4<T>& o, const sp4<T>& J, const pol3<T>& e) {
+  const cx<T>&L0 = J.c[0], &L1 = J.c[1], &R0 = J.c[2], &R1 = J.c[3];
+  o.c[0].r = o.c[0].r - e.e3 * R0.r - e.e1 * R1.r - e.e2 * R1.i;
+  o.c[0].i = o.c[0].i - e.e3 * R0.i - e.e1 * R1.i + e.e2 * R1.r;
+  o.c[1].r = o.c[1].r - e.e1 * R0.r + e.e2 * R0.i + e.e3 * R1.r;
+  o.c[1].i = o.c[1].i - e.e1 * R0.i - e.e2 * R0.r + e.e3 * R1.i;
+  o.c[2].r = o.c[2].r + e.e3 * L0.r + e.e1 * L1.r + e.e2 * L1.i;
+  o.c[2].i = o.c[2].i + e.e3 * L0.i + e.e1 * L1.i - e.e2 * L1.r;
+  o.c[3].r = o.c[3].r + e.e1 * L0.r - e.e2 * L0.i - e.e3 * L1.r;
+  o.c[3].i = o.c[3].i + e.e1 * L0.i + e.e2 * L0.r - e.e3 * L1.i;
+}
+// The join with the row current written as the column (-B1, B0, -B3, B2):
+// acc += X1 Y0 - X0 Y1 + X3 Y2 - X2 Y3 (antisymmetric in X, Y).        32 FLOPs
+template <class T> QEDX_HD void pair_acc(cx<T>& acc, const sp4<T>& X, const sp4<T>& Y) {
+  T r = acc.r, i = acc.i;
+#pragma unroll
+  for (int k = 0; k < 4; k += 2) {
+    const cx<T>&x0 = X.c[k], &x1 = X.c[k + 1], &y0 = Y.c[k], &y1 = Y.c[k + 1];
+    r = r + x1.r * y0.r - x0.r * y1.r - x1.i * y0.i + x0.i * y1.i;
+    i = i + x1.r * y0.i - x0.r * y1.i + x1.i * y0.r - x0.i * y1.r;
+  }
+  acc.r = r;
+  acc.i = i;
+}
+#if defined(__HIP_DEVICE_COMPILE__)
+// A current in a wave's LDS region: component k of every lane at p[64 k]
+// (p already offset by the lane), 16 bytes per lane and access.
+__device__ inline void cur_put(double2* p, const sp4<double>& x) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) p[64 * k] = make_double2(x.c[k].r, x.c[k].i);
+}
+__device__ inline sp4<double> cur_get(const double2* p) {
+  sp4<double> x;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double2 t = p[64 * k];
+    x.c[k] = {t.x, t.y};
+  }
+  return x;
+}
+#endif
+
+}  // namespace qx

@@ -1,0 +1,65 @@
+"""The kernels with one current per photon subset, at the sizes where their
+tiling can go wrong, against the oracle.
+
+Per point (two lanes per point, 128 points per workgroup; five- and six-photon
+kernels loop over the points with one workgroup per compute unit): single
+points, the edges of a wave and of a workgroup, a ragged second round of the
+loop.  Tolerances are those of tests/parity.py, derived from the oracle's own
+cancellation.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_19456_amd import inputs
+from parity import check_fp64, per_point_ref
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("n_in,n", [(1, 1), (1, 2), (1, 3), (1, 4), (1, 5), (1, 6), (3, 1), (5, 1), (2, 3)])
+def test_per_point_tile_edges(n_in, n):
+    """Every size on a prefix of the same points: equal results wherever a
+    point lands in the grid, and the points at the edges against the oracle."""
+    from paper_2511_19456_amd.qedx import QedProcess
+    P = n + n_in
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    top = 128 * ncu + 129 if P in (5, 6) else 1000   # the loop's second round
+    if n_in == 1:
+        u, hel = inputs.rambo_inputs(70 + n, n, top, with_helicities=True)
+        mom = QedProcess(n, "per_point").rambo(torch.as_tensor(u, device=DEV), 6.0 + 3 * n)
+    elif n == 1:
+        m, hel = inputs.crossed_inputs(70 + n_in, n_in, top, with_helicities=True)
+        mom = torch.as_tensor(m, device=DEV)
+    else:  # one outgoing photon of e- gamma -> e- 4 gamma crossed into the initial state
+        u, _ = inputs.rambo_inputs(75, 4, top)
+        m = QedProcess(4, "per_point").rambo(torch.as_tensor(u, device=DEV), 9.0).view(7, 4, top)
+        mom = torch.cat([m[:2], -m[3:4], m[2:3], m[4:]]).reshape(28, top).contiguous()
+        hel = inputs.rng_for(76).integers(0, 1 << 7, size=top).astype(np.uint32)
+    p = QedProcess(n, "per_point", n_in=n_in)
+    hd = torch.as_tensor(hel.astype(np.int32), device=DEV)
+    full = p.eval(mom, hd)
+    for N in (1, 2, 31, 32, 33, 127, 128, 129, top - 1):
+        out = torch.full((N + 1,), -7.0, dtype=torch.float64, device=DEV)
+        p.eval(mom[:, :N].contiguous(), hd[:N].contiguous(), out=out[:N])
+        assert torch.equal(out[:N], full[:N]) and out[N].item() == -7.0, N
+    idx = np.unique([0, 1, 31, 32, 63, 127, 128, top // 2, max(0, top - 129), top - 2, top - 1])
+    ref, kap = per_point_ref(mom[:, idx].cpu().numpy(), n, hel[idx], n_in=n_in)
+    check_fp64(full[idx].cpu().numpy(), ref, kap, f"{n_in} -> {n}")
+
+
+def test_per_point_every_configuration_sums_to_the_helicity_sum():
+    """All 2^(n+3) configurations of a point, one per lane pair, against the
+    oracle's helicity sum (spin and polarisation codes of every particle)."""
+    from oracle import qed_oracle as O
+    from paper_2511_19456_amd.qedx import QedProcess
+    n, k = 3, 5
+    u, _ = inputs.rambo_inputs(77, n, k)
+    mom = O.momenta_soa_from_uniforms(u, 10.0, n)
+    hel = np.tile(np.arange(64, dtype=np.int32), k)
+    mm = torch.as_tensor(np.repeat(mom.numpy(), 64, axis=1), device=DEV)
+    got = QedProcess(n, "per_point").eval(mm, torch.as_tensor(hel, device=DEV)).view(k, 64).sum(1).cpu().numpy()
+    ref = O.m2(mom, n, "sum").numpy()
+    assert np.abs(got / ref - 1).max() < 1e-10
