@@ -73,11 +73,14 @@ typedef enum { QED_HEL_SUM = 0, QED_HEL_PER_POINT = 1 } qed_hel_mode;
 typedef enum { QED_FP64 = 0, QED_FP32C = 1 } qed_precision;
 
 /* Kernel shape knobs (a zero field = library default for the process).
- * FP64 per-point kernels for which no shape is given (lane_bits, loop_bits,
+ * FP64 evaluation kernels for which no shape is given (lane_bits, loop_bits,
  * block, split, min_waves, order, partial all zero) sum the photon orderings
- * of each photon subset before the next vertex (one current per subset, two
- * lanes per point), with rewrite 0 and 1 alike; a given shape selects the
- * kernels that follow the graph node by node.
+ * of each photon subset before the next vertex (one current per subset), with
+ * rewrite 0 and 1 alike: per point two lanes per point, one per electron;
+ * helicity sums of up to 5 photons 4 to 32 lanes sharing the currents, for one
+ * spin of e-_in and doubled (flipping both electron spins conjugates the
+ * amplitude).  A given shape selects the kernels that follow the graph node
+ * by node.
  * lane_bits:  helicity bits spread over lanes (2^popcount lanes per point),
  *             given as a mask over particle bits; SUM mode only.
  * loop_bits:  helicity bits enumerated by a run-time loop; SUM mode only.

@@ -28,7 +28,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libqedx.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
-HOST_SOURCES = ["qedx_dag.cpp", "qedx_emit.cpp", "qedx_pair.cpp", "qedx_kernels.cpp", "qedx_runtime.cpp", "qedx_batch.cpp",
+HOST_SOURCES = ["qedx_dag.cpp", "qedx_emit.cpp", "qedx_pair.cpp", "qedx_coop.cpp", "qedx_kernels.cpp", "qedx_runtime.cpp", "qedx_batch.cpp",
                 "qedx_hosttools.cpp"]
 # measurement tool kept out of the evaluation library (include/qedx_probe.h)
 PROBE_SOURCES = ["qedx_probe.cpp"]

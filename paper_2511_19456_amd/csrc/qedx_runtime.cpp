@@ -33,6 +33,7 @@
 #include "qedx_internal.hpp"
 #include "qedx_scratch.hpp"
 #include "qedx_kernels.hpp"
+#include "qedx_coop.hpp"
 #include "qedx_pair.hpp"
 
 extern char** environ;
@@ -452,9 +453,12 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
     auto t0 = std::chrono::steady_clock::now();
     EmitStats st;
     const bool pair = prec == QED_FP64 && pair_kernel(proc, v);
-    src = pair ? emit_pair_kernel(proc, v, eval_kernel_name(n, nin, mode, prec, v), &st)
-               : emit_eval_kernel(d, v, eval_kernel_name(n, nin, mode, prec, v), &st);
-    info.lanes_per_point = pair ? 2 : lanes_per_point(v);
+    const bool coop = coop_kernel(proc, v);
+    const std::string kname = eval_kernel_name(n, nin, mode, prec, v);
+    src = pair ? emit_pair_kernel(proc, v, kname, &st)
+               : coop ? emit_coop_kernel(proc, v, kname, &st) : emit_eval_kernel(d, v, kname, &st);
+    info.lanes_per_point = pair ? 2 : coop ? coop_lanes(proc) : lanes_per_point(v);
+    info.block = coop ? kCoopBlock : v.block;
     info.create_ms_emit = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     info.n_V = st.n_V;
     info.n_S1 = st.n_S1;
@@ -467,7 +471,6 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
   info.n = n;
   info.mode = mode;
   info.precision = prec;
-  info.block = v.block;
   std::string tag = variant_tag(v, n, nin);
   snprintf(info.kernel_tag, sizeof info.kernel_tag, "%s", tag.c_str());
   snprintf(info.kernel_name, sizeof info.kernel_name, "%s", eval_kernel_name(n, nin, mode, prec, v).c_str());
@@ -656,8 +659,8 @@ extern "C" qed_status qed_eval(const qed_process* p, const double* momenta, cons
   if (!p->f_fix) {
     void* args[] = {(void*)&momenta, (void*)&hel, (void*)&n, (void*)&out};
     int64_t threads = N * (int64_t)p->lanes;
-    if (p->max_groups) threads = std::min(threads, p->max_groups * (int64_t)p->var.block);
-    return launch(p->f_eval, threads, p->var.block, stream, args);
+    if (p->max_groups) threads = std::min(threads, p->max_groups * (int64_t)p->info.block);
+    return launch(p->f_eval, threads, p->info.block, stream, args);
   }
   // FP32C pass, which marks the points it cannot resolve with a negative
   // value in `out`, then the FP64 pass over those marks (one workgroup per

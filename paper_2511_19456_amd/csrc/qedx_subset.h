@@ -45,6 +45,46 @@ __device__ inline sp4<double> cur_get(const double2* p) {
   }
   return x;
 }
+
+// Shared-current kernels: component k of a current at p[NC k]; polarisation
+// vector i of NP in NP pairs (e1, e2) and the NP e3 after them; propagator
+// coefficients at p[0], p[D], p[2 D].
+template <int NC> __device__ inline sp4<double> cur_at(const double2* p) {
+  sp4<double> x;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double2 t = p[NC * k];
+    x.c[k] = {t.x, t.y};
+  }
+  return x;
+}
+template <int NC> __device__ inline void cur_to(double2* p, const sp4<double>& x) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) p[NC * k] = make_double2(x.c[k].r, x.c[k].i);
+}
+template <int NP> __device__ inline pol3<double> pol_at(const double2* p, unsigned i) {
+  const double2 a = p[i];
+  return {a.x, a.y, ((const double*)(p + NP))[i]};
+}
+template <int D> __device__ inline propq<double> prop_at(const double2* p) {
+  const double2 a = p[0], b = p[D];
+  return {a.x, a.y, b.x, b.y, p[2 * D].x};
+}
+// Orders the wave's LDS accesses (the hardware keeps them in program order).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// Workgroups go round the 8 XCDs in turn; neighbouring tiles, which share
+// cache lines of the momenta, are kept on one XCD and its L2.
+__device__ inline long long xcd_tile() {
+  const unsigned n = gridDim.x, per = (n + 7u) >> 3, full = n & 7u;
+  const unsigned x = blockIdx.x & 7u, i = blockIdx.x >> 3;
+  // XCDs below `full` (all of them if it is 0) hold per tiles, the others per - 1
+  const unsigned lo = full == 0u || x <= full ? x * per : full * per + (x - full) * (per - 1u);
+  return (long long)lo + i;
+}
 #endif
 
 }  // namespace qx

@@ -63,3 +63,30 @@ def test_per_point_every_configuration_sums_to_the_helicity_sum():
     got = QedProcess(n, "per_point").eval(mm, torch.as_tensor(hel, device=DEV)).view(k, 64).sum(1).cpu().numpy()
     ref = O.m2(mom, n, "sum").numpy()
     assert np.abs(got / ref - 1).max() < 1e-10
+
+
+@pytest.mark.parametrize("n_in,n", [(1, 1), (1, 2), (1, 3), (1, 4), (2, 2), (4, 1)])
+def test_helicity_sum_tile_edges(n_in, n):
+    from oracle import qed_oracle as O
+    from paper_2511_19456_amd.qedx import QedProcess
+    top = 151
+    if n_in == 1:
+        u, _ = inputs.rambo_inputs(80 + n, n, top)
+        mom = O.momenta_soa_from_uniforms(u, 5.0 + 3 * n, n).numpy()
+    elif n == 1:
+        mom, _ = inputs.crossed_inputs(80 + n_in, n_in, top)
+    else:
+        u, _ = inputs.rambo_inputs(85, 3, top)
+        m = O.momenta_from_uniforms(u, 9.0, 3)
+        mom = O.points_to_soa(torch.cat([m[:, :2], -m[:, 3:4], m[:, 2:3], m[:, 4:]], dim=1)).numpy()
+    p = QedProcess(n, "sum", n_in=n_in)
+    md = torch.as_tensor(mom, device=DEV)
+    full = p.eval(md)
+    ref = O.m2(mom, n, "sum", n_in=n_in).numpy()
+    assert np.abs(full.cpu().numpy() / ref - 1).max() < 1e-10
+    w = 64 // p.info()["lanes_per_point"]
+    sizes = {1, 2, w - 1, w, w + 1} | {w * k for k in range(2, 10)} | {w * 7 + 1, w * 8 + 1, top - 1}
+    for N in sorted(s for s in sizes if 0 < s < top):
+        out = torch.full((N + 1,), -7.0, dtype=torch.float64, device=DEV)
+        p.eval(md[:, :N].contiguous(), out=out[:N])
+        assert torch.equal(out[:N], full[:N]) and out[N].item() == -7.0, N
