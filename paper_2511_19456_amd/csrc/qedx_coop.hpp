@@ -36,4 +36,25 @@ constexpr int kCoopBlock = 64;      // one wave per workgroup
 // extern "C" __global__ void <kname>(const double* mom, const unsigned* hel, long long N, double* out)
 std::string emit_coop_kernel(const Process& pr, const Variant& v, const std::string& kname, EmitStats* st);
 
+// Gradient of log sum |A|^2 for one incoming photon.  The forward levels, then
+// the same levels downwards with the adjoints in the currents' LDS slots; each
+// lane keeps the currents of its own items in registers (14 of them at 5
+// photons), so nothing is recomputed and LDS stays what the forward needs.  The
+// sums over items (40 polarisation and momentum gradients at 5 photons) are per
+// lane in registers and meet in LDS once, at the end.  At 5 photons 456
+// registers leave one wave per SIMD: VALU busy 0.58 of the time, LDS reads
+// take 0.43 of it (a third of that bank conflicts).  Measured against one walk
+// over the orderings per partition and electron: 5 photons, 2^18 points, 14.2 ->
+// 1.51 ms (16 lanes per point; 32 lanes 2.29); 4 photons, 2^19 points, 48.6 ->
+// 0.98 ms (a wave per SIMD instead of two, without 24 spilled registers: 1.26);
+// 3 photons 7.25 -> 0.34 ms, 2 photons 1.15 -> 0.21 ms.  With rambo: through the
+// phase-space map,
+//   <kname>(const double* u, double sqrt_s, long long N, double* logm2, double* grad, int tiles),
+// one wave per `tiles` (1 .. 64 / points of a wave) groups of points; without:
+//   <kname>(const double* mom, long long N, double* gm, double* logm2),
+// gm the final-state rows of the momentum gradient, one group per wave.
+// No device header included: the caller prepends it.
+std::string emit_coop_grad_kernel(const Process& pr, const std::string& kname, bool rambo, EmitStats* st);
+int coop_grad_lanes(const Process& pr);
+
 }  // namespace qedx

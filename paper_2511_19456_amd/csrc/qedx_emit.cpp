@@ -91,7 +91,6 @@ struct Emitter {
   EmitStats st;
   std::string T;
   std::string ind = "  ";
-  int mom_src = 0;  // 0: reload momenta from global memory; 1: opaque copies of registers M<p>_<mu>
   // Partition loop: one block for the canonical partition (photons 0..split-1
   // on the e-_in side) inside a run-time loop over all partitions; photon
   // slot a of iteration `it` is particle slot_tab[it][a], loaded per iteration.
@@ -137,7 +136,6 @@ struct Emitter {
   // one tile and one held current.
   std::map<int, std::string> alias;
   bool batch_mom = false;  // order flag 8192: block momenta loaded together (see block_momenta)
-  bool amp_store = false;  // body() also stores every configuration's amplitude
   bool stage() const { return (v.order & 16) != 0; }
   int lds_slots = 0;
   // partition slot loop: photon polarisation vectors computed once per point
@@ -854,12 +852,6 @@ struct Emitter {
     }
     // |A|^2, summed over the enumerated configurations (HelSum) or single
     for (size_t a = 0; a < sums.size(); ++a) {
-      if (amp_store) {
-        // staged in per-lane LDS (qx_as) and stored below: stores with
-        // their 64-bit addresses held while the accumulators are live spilled
-        os << ind << "qx_as[" << (2 * a) * v.block << " + threadIdx.x] = A" << a << ".r; qx_as[" << (2 * a + 1) * v.block
-           << " + threadIdx.x] = A" << a << ".i;\n";
-      }
       if (v.prec == PREC_F64) {
         os << ind << "acc += A" << a << ".r * A" << a << ".r + A" << a << ".i * A" << a << ".i;\n";
       } else {
@@ -877,22 +869,6 @@ struct Emitter {
         os << " }\n";
       }
       st.flops_per_point += 4;
-    }
-    if (amp_store) {
-      // amplitude of configuration hc | (the Sum's enumerated bits) to
-      // amp[2h][N], amp[2h+1][N] (shared e-_in side: lane 1's accumulators
-      // carry swapped e-_in labels).  Unguarded: a lane past the end computes
-      // point N-1 (ptc) exactly as that point's own lane does and stores the
-      // same bytes.
-      os << ind << "{\n" << ind << "  const unsigned qx_cf[" << sums.size() << "] = {";
-      for (size_t a = 0; a < sums.size(); ++a) os << (a ? ", " : "") << d.nodes[sums[a]].cfg << "u";
-      os << "};\n";
-      std::string flip = coop ? " ^ (((hc >> " + std::to_string(pr.i_eout) + ") & 1u) << " + std::to_string(pr.i_ein) + ")" : "";
-      os << ind << "  #pragma unroll 4\n" << ind << "  for (int a = 0; a < " << sums.size() << "; ++a) {\n";
-      os << ind << "    const unsigned hh = hc | (qx_cf[a]" << flip << ");\n";
-      os << ind << "    amp[(2 * hh) * N + ptc] = qx_as[2 * a * " << v.block << " + threadIdx.x];\n";
-      os << ind << "    amp[(2 * hh + 1) * N + ptc] = qx_as[(2 * a + 1) * " << v.block << " + threadIdx.x];\n";
-      os << ind << "  }\n" << ind << "}\n";
     }
   }
 
@@ -1003,599 +979,9 @@ struct Emitter {
   std::string mj_tables;
   static constexpr int kMjStride = 65;  // doubles per lane in the staging area (padded against bank conflicts)
 
-  // ---------------------------------------------------------------------
-  // Adjoint pass.  Per partition block: the e-_in-side leaves are recomputed
-  // and held; the e-_out-side prefix trie is walked depth first, recomputing
-  // each current from its parent, taking the dots at its leaves and folding
-  // each node's adjoint into its parent on the way back; then the e-_in-side
-  // trie is walked the same way with the leaf adjoints gathered at the dots.
-  // Only the current path is live: currents are recomputed, not stored.
-  // ---------------------------------------------------------------------
-  std::set<int> blk;
-  std::map<int, std::vector<int>> cons;
-  std::set<int> leafJ;
-
-  bool final_particle(int p) const { return p == pr.i_eout || (p > pr.i_eout); }
-
-  // momentum-gradient accumulator of (particle p, component mu): a register,
-  // or a per-lane LDS slot when gm_in_lds is set (keeps it out of the
-  // register file during the adjoint sweep)
-  bool gm_in_lds = false;
-  std::string gmref(int p, int mu) const {
-    if (!gm_in_lds) return "gm" + std::to_string(p) + "_" + std::to_string(mu);
-    if (p < pr.i_eout) throw std::logic_error("gmref(): no gradient slot for an incoming particle");
-    return "qx_gm[" + std::to_string((4 * (p - pr.i_eout) + mu) * v.block) + " + threadIdx.x]";
-  }
-
-  // Polarisation-vector gradients of the walked side in per-lane LDS slots
-  // (ge_in_lds), allocated on first use; a polarisation whose gradient the
-  // block never touches gets no slot and no pol_vjp.
-  bool ge_in_lds = false;
-  const std::string ge_zero_mark = "//@GEZERO@\n";
-  std::map<int, int> ge_slot;
-  int ge_index(int x) {
-    auto it = ge_slot.find(x);
-    if (it != ge_slot.end()) return it->second;
-    int k = (int)ge_slot.size();
-    ge_slot[x] = k;
-    return k;
-  }
-  std::string geref(int slot, int c) const {
-    return "qx_ge[" + std::to_string((3 * slot + c) * v.block) + " + threadIdx.x]";
-  }
-  // vertex gradient with respect to the polarisation vector of node u
-  void emit_ge(const std::string& side, const std::string& w, const std::string& X, int u) {
-    if (!ge_in_lds) {
-      os << ind << "qx::v" << side << "_ge<double>(" << w << ", " << X << ", ge" << u << ");\n";
-      return;
-    }
-    const int k = ge_index(u);
-    os << ind << "{ qx::pol3<double> t = {0.0, 0.0, 0.0}; qx::v" << side << "_ge<double>(" << w << ", " << X
-       << ", t); " << addto(geref(k, 0), "t.e1") << " " << addto(geref(k, 1), "t.e2") << " " << addto(geref(k, 2), "t.e3")
-       << " }\n";
-  }
-
-  // Propagator-coefficient gradients accumulated per distinct propagator
-  // (side, photon set) in per-lane LDS, across every iteration of the
-  // kernel, and mapped to momentum gradients once at its end (the map
-  // gq -> (gp, gK) is linear and depends on the momenta only).  Keeps the
-  // propagator kinematics out of the registers of the adjoint walk.
-  bool gq_in_lds = false;
-  std::map<std::pair<int, uint32_t>, int> gq_slot;
-  int gq_index(int side, uint32_t mask) {
-    auto it = gq_slot.find({side, mask});
-    if (it != gq_slot.end()) return it->second;
-    int k = (int)gq_slot.size();
-    gq_slot[{side, mask}] = k;
-    return k;
-  }
-  std::string gqref(int slot, int c) const {
-    return "qx_gq[" + std::to_string((5 * slot + c) * v.block) + " + threadIdx.x]";
-  }
-
-  // statement adding val (negated if neg) to the accumulator ref: +=, or,
-  // with lds_atomic set, for a per-lane LDS slot (qx_*) an LDS atomic add
-  // whose result is not read (ds_add_f64: no read-modify-write round trip
-  // for the wave to wait on; each slot belongs to one lane, so the adds keep
-  // program order).  Measured per kernel: faster in the e-_out-side walks,
-  // slower in the e-_in-side ones (whose repeated adds to one slot the
-  // compiler otherwise merges in registers).
-  bool lds_atomic = false;
-  std::string addto(const std::string& ref, const std::string& val, bool neg = false) const {
-    if (!lds_atomic || ref.compare(0, 3, "qx_") != 0) return ref + (neg ? " -= " : " += ") + val + ";";
-    return "__hip_atomic_fetch_add(&" + ref + ", " + (neg ? "-(" + val + ")" : val) +
-           ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);";
-  }
-
-  void collect_block(const std::vector<int>& dk) {
-    blk.clear();
-    cons.clear();
-    std::vector<int> stk(dk.begin(), dk.end());
-    while (!stk.empty()) {
-      int x = stk.back();
-      stk.pop_back();
-      if (blk.count(x)) continue;
-      blk.insert(x);
-      for (int p : d.nodes[x].in) {
-        int pp = producer(p);
-        if (d.nodes[pp].kind == Kind::Entry) continue;
-        cons[pp].push_back(x);
-        stk.push_back(pp);
-      }
-    }
-  }
-
-  std::string fname(int x) const { return (done[x] ? "n" : "f") + std::to_string(x); }
-
-  // signed photon-momentum sum K of a propagator, in Kl0..Kl3.  opaque: the
-  // values pass through an empty asm, so the compiler cannot merge equal
-  // sums (and the propagator set-up that follows) across the scopes of an
-  // adjoint walk and keep them live from one scope to the next; each scope
-  // recomputes its own.
-  void emit_K_inline(uint32_t mask, bool opaque = false) {
-    for (int mu = 0; mu < 4; ++mu) {
-      os << ind << (opaque ? "double Kl" : "const double Kl") << mu << " = 0.0";
-      for (int a = 0; a < pr.P; ++a)
-        if ((mask >> a) & 1)
-          os << (pr.photon_sign[a] > 0 ? " + " : " - ") << "m" << pr.photon_particle[a] << "_" << mu;
-      os << ";\n";
-    }
-    if (opaque) os << ind << "asm volatile(\"\" : \"+v\"(Kl0), \"+v\"(Kl1), \"+v\"(Kl2), \"+v\"(Kl3));\n";
-  }
-
-  void prop_grad_to_momenta(int side, uint32_t mask) {
-    int pe = side == 0 ? pr.i_ein : pr.i_eout;
-    std::string m = "m" + std::to_string(pe) + "_";
-    os << ind << "{ double gp[4] = {0.0, 0.0, 0.0, 0.0}, gK[4] = {0.0, 0.0, 0.0, 0.0};\n";
-    os << ind << "  qx::prop_from_vjp(" << m << "0, " << m << "1, " << m << "2, " << m << "3, Kl0, Kl1, Kl2, Kl3, "
-       << (side == 0 ? "1.0" : "-1.0") << ", 1.0, gq, gp, gK);\n";
-    if (final_particle(pe))
-      for (int mu = 0; mu < 4; ++mu) os << ind << "  " << addto(gmref(pe, mu), "gp[" + std::to_string(mu) + "]") << "\n";
-    for (int a = 0; a < pr.P; ++a)
-      if (((mask >> a) & 1) && final_particle(pr.photon_particle[a]))
-        for (int mu = 0; mu < 4; ++mu)
-          os << ind << "  "
-             << addto(gmref(pr.photon_particle[a], mu), "gK[" + std::to_string(mu) + "]", pr.photon_sign[a] < 0) << "\n";
-    os << ind << "}\n";
-  }
-
-  // momentum gradients of every accumulated propagator (end of the kernel;
-  // momenta m<p>_<mu> in scope)
-  void flush_gq() {
-    for (auto& kv : gq_slot) {
-      const int side = kv.first.first;
-      const uint32_t mask = kv.first.second;
-      os << ind << "{\n";
-      std::string o = ind;
-      ind += "  ";
-      emit_K_inline(mask);
-      const char* f[5] = {"qm", "qp", "q1", "q2", "mm"};
-      os << ind << "qx::propq<double> gq;\n";
-      for (int c = 0; c < 5; ++c) os << ind << "gq." << f[c] << " = " << gqref(kv.second, c) << ";\n";
-      prop_grad_to_momenta(side, mask);
-      ind = o;
-      os << ind << "}\n";
-    }
-  }
-
-  // Emit the adjoint contribution of consumer c (of current x) into w<x>.
-  void rev(int c, int x) {
-    const Node& n = d.nodes[c];
-    if (n.kind == Kind::Dot) {
-      auto ops = dot_ops(n);
-      int J = producer(ops.first), B = producer(ops.second);
-      int sum = d.nodes[n.out[0]].out[0];
-      os << ind << "qx::dot_vjp<double>(c" << acc_of_sum.at(sum) << ", " << fname(B) << ", " << fname(J) << ", w" << B
-         << ", w" << J << ");\n";
-      st.flops_per_point += 64;
-      return;
-    }
-    const std::string X = fname(x);
-    os << ind << "{\n";
-    std::string outer = ind;
-    ind += "  ";
-    const bool leaf = leafJ.count(c) > 0;
-    // adjoint of c: its own accumulator, or (factored block, column leaf)
-    // the seed shared by the leaves of its configurations
-    const std::string wc = (leaf && factored) ? "W" + std::to_string(memJ.at(c)) : "w" + std::to_string(c);
-    if (n.kind == Kind::S1) {
-      emit_K_inline(n.mask, true);
-      int pe = n.side == 0 ? pr.i_ein : pr.i_eout;
-      std::string m = "m" + std::to_string(pe) + "_";
-      os << ind << "const qx::propq<double> q = qx::prop_from<double>(" << m << "0, " << m << "1, " << m << "2, " << m
-         << "3, Kl0, Kl1, Kl2, Kl3, " << (n.side == 0 ? "1.0" : "-1.0") << ", 1.0);\n";
-      st.flops_per_point += 28;
-    }
-    const std::string side = n.side == 0 ? "L" : "R", other = n.side == 0 ? "R" : "L";
-    std::string E;
-    if (n.kind == Kind::V) E = "n" + std::to_string(producer(n.in[0]));
-    if (!leaf) {
-      if (n.kind == Kind::V)
-        os << ind << "const qx::sp4<double> f" << c << " = qx::v" << side << "<double>(" << X << ", " << E << ");\n";
-      else
-        os << ind << "const qx::sp4<double> f" << c << " = qx::s" << side << "<double>(" << X << ", q);\n";
-      if (factored && memB.count(c)) {
-        // row leaf of a factored block: its adjoint is the row seed of its
-        // configurations; in the one-kernel sweep it also joins their row
-        // sum (the split e-_in-side kernel recomputes those sums itself)
-        os << ind << "const qx::sp4<double> w" << c << " = T" << memB.at(c) << ";\n";
-        if (grad_phase == 0) {
-          os << ind << "qx::add_to(SB" << memB.at(c) << ", f" << c << ");\n";
-          st.flops_per_point += 8;
-        }
-        st.flops_per_point += n.kind == Kind::V ? 40 : 56;
-      } else {
-        os << ind << "qx::sp4<double> w" << c << " = qx::zero4<double>();\n";
-        st.flops_per_point += n.kind == Kind::V ? 40 : 56;
-        for (int c2 : cons[c]) rev(c2, c);
-      }
-    }
-    if (n.kind == Kind::V) {
-      os << ind << "qx::add_to(w" << x << ", qx::v" << other << "<double>(" << wc << ", " << E << "));\n";
-      st.flops_per_point += 40;
-      // polarisation gradient, for final-state photons only (the incoming
-      // photon's momentum is fixed)
-      if (final_particle(d.nodes[producer(n.in[0])].particle)) {
-        emit_ge(side, wc, X, producer(n.in[0]));
-        st.flops_per_point += 48;
-      }
-    } else {
-      os << ind << "qx::add_to(w" << x << ", qx::s" << other << "<double>(" << wc << ", q));\n";
-      os << ind << "qx::propq<double> gq = {0.0, 0.0, 0.0, 0.0, 0.0};\n";
-      os << ind << "qx::s" << side << "_gq<double>(" << wc << ", " << X << ", gq);\n";
-      if (gq_in_lds) {
-        const int k = gq_index(n.side, n.mask);
-        const char* f[5] = {"qm", "qp", "q1", "q2", "mm"};
-        for (int c = 0; c < 5; ++c) os << ind << addto(gqref(k, c), std::string("gq.") + f[c]) << "\n";
-      } else {
-        prop_grad_to_momenta(n.side, n.mask);
-      }
-      st.flops_per_point += 56 + 64 + 60;
-    }
-    ind = outer;
-    os << ind << "}\n";
-  }
-
-  // ---------------------------------------------------------------------
-  // Adjoint over a distributed graph (subset currents).  Its currents form a
-  // DAG (an Add has several parents), so the sweep runs top-down from each
-  // join: a node's adjoint is pushed to its inputs, recomputing the forward
-  // value of an input where a parameter gradient needs it.  Nothing but the
-  // adjoints of the current path is held.
-  // ---------------------------------------------------------------------
-  int tmpc = 0;
-  std::string tmpname(const char* p) { return std::string(p) + std::to_string(tmpc++); }
-
-  // statements computing the value of current node x; returns the variable
-  std::string fwd(int x) {
-    x = producer(x);
-    const Node& n = d.nodes[x];
-    std::string v = tmpname("f");
-    switch (n.kind) {
-      case Kind::U:
-        emit(x);
-        return name(x);
-      case Kind::V: {
-        std::string y = fwd(n.in[1]);
-        bool yp = d.nodes[producer(n.in[0])].hel == 1;
-        os << ind << "const qx::sp4<double> " << v << " = qx::v" << (n.side == 0 ? "L" : "R") << (yp ? "_y" : "")
-           << "<double>(" << y << ", " << name(n.in[0]) << ");\n";
-        st.flops_per_point += yp ? 24 : 40;
-        return v;
-      }
-      case Kind::S1: {
-        std::string y = fwd(n.in[0]);
-        os << ind << "qx::sp4<double> " << v << ";\n" << ind << "{\n";
-        std::string o = ind;
-        ind += "  ";
-        emit_K_inline(n.mask);
-        int pe = n.side == 0 ? pr.i_ein : pr.i_eout;
-        std::string m = "m" + std::to_string(pe) + "_";
-        os << ind << "const qx::propq<double> q = qx::prop_from<double>(" << m << "0, " << m << "1, " << m << "2, " << m
-           << "3, Kl0, Kl1, Kl2, Kl3, " << (n.side == 0 ? "1.0" : "-1.0") << ", 1.0);\n";
-        os << ind << v << " = qx::s" << (n.side == 0 ? "L" : "R") << "<double>(" << y << ", q);\n";
-        ind = o;
-        os << ind << "}\n";
-        st.flops_per_point += 28 + 56;
-        return v;
-      }
-      case Kind::Add: {
-        std::string e = fwd(n.in[0]);
-        for (size_t t = 1; t < n.in.size(); ++t) e = "qx::add4<double>(" + e + ", " + fwd(n.in[t]) + ")";
-        os << ind << "const qx::sp4<double> " << v << " = " << e << ";\n";
-        st.flops_per_point += 8.0 * (double)(n.in.size() - 1);
-        return v;
-      }
-      default:
-        throw std::logic_error("fwd(): not a current");
-    }
-  }
-
-  // push adjoint w of current node x to its inputs and to the momentum gradient
-  void adj(int x, const std::string& w) {
-    x = producer(x);
-    const Node& n = d.nodes[x];
-    switch (n.kind) {
-      case Kind::U:
-        if (n.particle == pr.i_eout) {
-          std::string m = "m" + std::to_string(pr.i_eout) + "_";
-          os << ind << "{ double g[4]; qx::ubar_vjp(" << m << "0, " << m << "1, " << m << "2, " << m << "3, "
-             << hel_expr(n) << ", 1.0, " << w << ", g);\n";
-          for (int mu = 0; mu < 4; ++mu) os << ind << "  " << addto(gmref(pr.i_eout, mu), "g[" + std::to_string(mu) + "]") << "\n";
-          os << ind << "}\n";
-        }
-        return;
-      case Kind::Add:
-        for (int y : n.in) adj(y, w);
-        return;
-      case Kind::V: {
-        os << ind << "{\n";
-        std::string o = ind;
-        ind += "  ";
-        const std::string side = n.side == 0 ? "L" : "R", other = n.side == 0 ? "R" : "L";
-        std::string y = fwd(n.in[1]);
-        os << ind << "qx::v" << side << "_ge<double>(" << w << ", " << y << ", ge" << producer(n.in[0]) << ");\n";
-          std::string wy = tmpname("w");
-        os << ind << "const qx::sp4<double> " << wy << " = qx::v" << other << "<double>(" << w << ", "
-           << name(n.in[0]) << ");\n";
-        st.flops_per_point += 48 + 40;
-        adj(n.in[1], wy);
-        ind = o;
-        os << ind << "}\n";
-        return;
-      }
-      case Kind::S1: {
-        os << ind << "{\n";
-        std::string o = ind;
-        ind += "  ";
-        const std::string side = n.side == 0 ? "L" : "R", other = n.side == 0 ? "R" : "L";
-        std::string y = fwd(n.in[0]);
-        emit_K_inline(n.mask);
-        int pe = n.side == 0 ? pr.i_ein : pr.i_eout;
-        std::string m = "m" + std::to_string(pe) + "_";
-        os << ind << "const qx::propq<double> q = qx::prop_from<double>(" << m << "0, " << m << "1, " << m << "2, " << m
-           << "3, Kl0, Kl1, Kl2, Kl3, " << (n.side == 0 ? "1.0" : "-1.0") << ", 1.0);\n";
-        os << ind << "qx::propq<double> gq = {0.0, 0.0, 0.0, 0.0, 0.0};\n";
-        os << ind << "qx::s" << side << "_gq<double>(" << w << ", " << y << ", gq);\n";
-        prop_grad_to_momenta(n.side, n.mask);
-        std::string wy = tmpname("w");
-        os << ind << "const qx::sp4<double> " << wy << " = qx::s" << other << "<double>(" << w << ", q);\n";
-        st.flops_per_point += 28 + 64 + 60 + 56;
-        adj(n.in[0], wy);
-        ind = o;
-        os << ind << "}\n";
-        return;
-      }
-      default:
-        throw std::logic_error("adj(): not a current");
-    }
-  }
-
-  void dist_adjoint_block(uint32_t key, const std::vector<int>& dk) {
-    os << ind << "// adjoint (subset currents): photons " << key << " | " << (((1u << pr.P) - 1) & ~key) << "\n";
-    std::string outer = open_block();
-    flush_seeds();
-    std::vector<int> pols;
-    for (size_t i = 0; i < d.nodes.size(); ++i) {
-      const Node& n = d.nodes[i];
-      if (n.kind == Kind::U && n.particle != pr.i_ein && n.particle != pr.i_eout) {
-        emit((int)i);
-        os << ind << "qx::pol3<double> ge" << i << " = {0.0, 0.0, 0.0};\n";
-        pols.push_back((int)i);
-      }
-    }
-    for (int k : dk) {
-      const Node& dn = d.nodes[k];
-      auto ops = dot_ops(dn);
-      int sum = d.nodes[dn.out[0]].out[0];
-      std::string jv = fwd(ops.first), bv = fwd(ops.second);
-      std::string wj = tmpname("w"), wb = tmpname("w");
-      os << ind << "qx::sp4<double> " << wj << " = qx::zero4<double>(), " << wb << " = qx::zero4<double>();\n";
-      os << ind << "qx::dot_vjp<double>(c" << acc_of_sum.at(sum) << ", " << bv << ", " << jv << ", " << wb << ", " << wj
-         << ");\n";
-      st.flops_per_point += 64;
-      adj(ops.second, wb);
-      adj(ops.first, wj);
-    }
-    for (int u : pols) {
-      const Node& n = d.nodes[u];
-      if (!final_particle(n.particle)) continue;
-      std::string m = "m" + std::to_string(n.particle) + "_";
-      os << ind << "{ double g[3]; qx::pol_vjp(" << m << "1, " << m << "2, " << m << "3, " << hel_expr(n) << ", ge" << u
-         << ", g);\n";
-      for (int mu = 1; mu < 4; ++mu) os << ind << "  " << addto(gmref(n.particle, mu), "g[" + std::to_string(mu - 1) + "]") << "\n";
-      os << ind << "}\n";
-    }
-    close_block(outer);
-  }
-
-  // Factored adjoint of a partition block.  For each configuration a the
-  // block's dots pair every row leaf B of a with every column leaf J of a
-  // (all orderings of the photons on either side), so the block's share of
-  // the amplitude is A_a = (sum_B B) . (sum_J J) and its adjoint needs only
-  // the sums: w_B = sum_{a: B in a} c_a SJ_a, w_J = sum_{a: J in a} c_a SB_a.
-  // No leaf or leaf adjoint is held across the other side's sweep; the
-  // sums are kept per membership pattern (the set of configurations a leaf
-  // belongs to, a bit mask over the block's accumulators).
-  bool factored = false;
-  std::map<int, uint32_t> memB, memJ;
-
-  bool factor_block(const std::vector<int>& dk) {
-    memB.clear();
-    memJ.clear();
-    std::map<int, std::set<std::pair<int, int>>> pairs;
-    for (int k : dk) {
-      const Node& dn = d.nodes[k];
-      if (dn.kind != Kind::Dot) return false;
-      auto ops = dot_ops(dn);
-      int J = producer(ops.first), B = producer(ops.second);
-      int a = acc_of_sum.at(d.nodes[dn.out[0]].out[0]);
-      if (a >= 32 || !pairs[a].insert({B, J}).second) return false;
-      memB[B] |= 1u << a;
-      memJ[J] |= 1u << a;
-    }
-    for (auto& kv : pairs) {
-      std::set<int> Bs, Js;
-      for (auto& bj : kv.second) {
-        Bs.insert(bj.first);
-        Js.insert(bj.second);
-      }
-      if (kv.second.size() != Bs.size() * Js.size()) return false;
-    }
-    for (auto& kv : memB) {
-      const Node& b = d.nodes[kv.first];
-      if (b.kind != Kind::S1 && b.kind != Kind::V) return false;
-      for (int c2 : cons[kv.first])
-        if (d.nodes[c2].kind != Kind::Dot) return false;
-    }
-    return true;
-  }
-
-  // sum over the configurations a in `pat` of c_a times the patterns' sums
-  // S<q> of every pattern q containing a
-  void emit_seed(const std::string& out, uint32_t pat, const std::string& S, const std::set<uint32_t>& pats,
-                 bool declare = true) {
-    if (declare) os << ind << "qx::sp4<double> " << out << " = qx::zero4<double>();\n";
-    for (int a = 0; a < 32; ++a) {
-      if (!((pat >> a) & 1)) continue;
-      for (uint32_t q : pats)
-        if ((q >> a) & 1) {
-          os << ind << "qx::axpy<double>(" << out << ", c" << a << ", " << S << q << ");\n";
-          st.flops_per_point += 32;
-        }
-    }
-  }
-
-  // Split adjoint kernels (grad_phase): 0 = the whole partition sweep; 1 =
-  // the e-_out-side walk; 2 = the e-_in-side walk.  Each of the two kernels
-  // holds only its own walk's state: the seeds of its side come from a
-  // forward walk of the other side's trie in a scope of its own (its leaf
-  // sums), so nothing passes between the two kernels but the momentum
-  // gradients they add.
-  int grad_phase = 0;
-  // Split kernels whose walked side has no looped photon: the walk's forward
-  // currents are the same in every loop iteration and its adjoints are
-  // linear in the seeds, so the seeds are summed over the iterations
-  // (merge_part 1, inside the loop: the other side's leaf sums and the seed
-  // sums) and the side is walked once (merge_part 2, after the loop).
-  int merge_part = 0;
-  // statements defining the adjoint seeds c<a> (partition adjoint kernels),
-  // emitted by the block where it first needs them
-  std::string seed_code;
-  void flush_seeds() {
-    std::istringstream in(seed_code);
-    for (std::string line; std::getline(in, line);) os << ind << line << "\n";
-    seed_code.clear();
-  }
-
-  // forward walk of the leaves `leaves` (node -> pattern) in a scope of its
-  // own, summing them per pattern into <S><pattern>; its currents die with
-  // the scope (the adjoint walk recomputes what it needs)
-  void leaf_sums(const std::map<int, uint32_t>& leaves, const std::string& S, const std::set<uint32_t>& pats) {
-    for (uint32_t q : pats) os << ind << "qx::sp4<double> " << S << q << " = qx::zero4<double>();\n";
-    os << ind << "{\n";
-    std::string o = ind;
-    ind += "  ";
-    std::vector<char> done0 = done;
-    std::set<uint32_t> kdone0 = kdone;
-    std::set<std::pair<int, uint32_t>> qdone0 = qdone;
-    for (auto& kv : leaves) {
-      emit(kv.first);
-      os << ind << "qx::add_to(" << S << kv.second << ", " << name(kv.first) << ");\n";
-      st.flops_per_point += 8;
-    }
-    done = done0;
-    kdone = kdone0;
-    qdone = qdone0;
-    ind = o;
-    os << ind << "}\n";
-  }
-
-  void grad_block(uint32_t key, const std::vector<int>& dk) {
-    collect_block(dk);
-    os << ind << "// adjoint: photons " << key << " | " << (((1u << pr.P) - 1) & ~key) << "\n";
-    std::string outer = open_block();
-    // polarisation-gradient accumulators of this block (registers, or LDS
-    // slots zeroed at the marker once the walk has allocated them)
-    for (int x : blk) {
-      const Node& n = d.nodes[x];
-      if (n.kind == Kind::U && n.particle != pr.i_ein && n.particle != pr.i_eout) {
-        emit(x);
-        if (!ge_in_lds && merge_part != 1) os << ind << "qx::pol3<double> ge" << x << " = {0.0, 0.0, 0.0};\n";
-      }
-    }
-    if (ge_in_lds && merge_part != 1) os << ge_zero_mark;
-    leafJ.clear();
-    for (int k : dk) leafJ.insert(producer(dot_ops(d.nodes[k]).first));
-    factored = factor_block(dk);
-    std::set<uint32_t> patB, patJ;
-    if (factored) {
-      for (auto& kv : memB) patB.insert(kv.second);
-      for (auto& kv : memJ) patJ.insert(kv.second);
-    }
-    if (merge_part == 1) {
-      // the other side's leaf sums and this iteration's share of the seeds
-      if (grad_phase == 2) {
-        leaf_sums(memB, "SB", patB);
-        flush_seeds();
-        for (uint32_t q : patJ) emit_seed("W" + std::to_string(q), q, "SB", patB, false);
-      } else {
-        leaf_sums(memJ, "SJ", patJ);
-        flush_seeds();
-        for (uint32_t q : patB) emit_seed("T" + std::to_string(q), q, "SJ", patJ, false);
-      }
-      close_block(outer);
-      return;
-    }
-    if (merge_part == 2) {
-      // seeds summed over the loop (declared by the kernel)
-    } else if (factored && grad_phase == 2) {
-      // the e-_out side's leaf sums, from a forward walk of the row trie
-      leaf_sums(memB, "SB", patB);
-      flush_seeds();
-    } else if (factored) {
-      // column sums per pattern, from a forward walk of the column trie
-      leaf_sums(memJ, "SJ", patJ);
-      flush_seeds();
-      // row seeds, and (one-kernel sweep) the row sums the row sweep
-      // accumulates
-      for (uint32_t q : patB) emit_seed("T" + std::to_string(q), q, "SJ", patJ);
-      if (grad_phase == 0)
-        for (uint32_t q : patB) os << ind << "qx::sp4<double> SB" << q << " = qx::zero4<double>();\n";
-    } else {
-      flush_seeds();
-      for (int J : leafJ) {
-        emit(J);
-        os << ind << "qx::sp4<double> w" << J << " = qx::zero4<double>();\n";
-      }
-    }
-    // e-_out side trie (dots at its leaves), then e-_in side trie
-    for (int pass = 0; pass < 2; ++pass) {
-      if ((grad_phase == 1 && pass == 1) || (grad_phase == 2 && pass == 0)) continue;
-      int root_particle = pass == 0 ? pr.i_eout : pr.i_ein;
-      if (pass == 1 && factored && merge_part != 2)
-        for (uint32_t q : patJ) emit_seed("W" + std::to_string(q), q, "SB", patB);
-      for (int r : blk) {
-        const Node& n = d.nodes[r];
-        if (n.kind != Kind::U || n.particle != root_particle) continue;
-        emit(r);
-        os << ind << "qx::sp4<double> w" << r << " = qx::zero4<double>();\n";
-        for (int c : cons[r]) rev(c, r);
-        if (pass == 0) {
-          std::string m = "m" + std::to_string(pr.i_eout) + "_";
-          os << ind << "{ double g[4]; qx::ubar_vjp(" << m << "0, " << m << "1, " << m << "2, " << m << "3, "
-             << hel_expr(n) << ", 1.0, w" << r << ", g);\n";
-          for (int mu = 0; mu < 4; ++mu) os << ind << "  " << addto(gmref(pr.i_eout, mu), "g[" + std::to_string(mu) + "]") << "\n";
-          os << ind << "}\n";
-        }
-      }
-    }
-    // polarisation vectors -> photon momenta
-    for (int x : blk) {
-      const Node& n = d.nodes[x];
-      if (n.kind == Kind::U && n.particle != pr.i_ein && n.particle != pr.i_eout && final_particle(n.particle)) {
-        std::string ge = "ge" + std::to_string(x);
-        if (ge_in_lds) {
-          auto it = ge_slot.find(x);
-          if (it == ge_slot.end()) continue;  // gradient never touched by this block
-          ge = "qx::pol3<double>{" + geref(it->second, 0) + ", " + geref(it->second, 1) + ", " +
-               geref(it->second, 2) + "}";
-        }
-        std::string m = "m" + std::to_string(n.particle) + "_";
-        os << ind << "{ double g[3]; qx::pol_vjp(" << m << "1, " << m << "2, " << m << "3, " << hel_expr(n) << ", " << ge
-           << ", g);\n";
-        for (int mu = 1; mu < 4; ++mu)
-          os << ind << "  " << addto(gmref(n.particle, mu), "g[" + std::to_string(mu - 1) + "]") << "\n";
-        os << ind << "}\n";
-      }
-    }
-    close_block(outer);
-  }
-
   // momenta for a partition-local block, opaque to the compiler
   void block_momenta() {
-    if (mom_src == 2) return;  // momenta already in m<p>_<mu> of the enclosing scope
-    if (mom_src == 0 && batch_mom) {
+    if (batch_mom) {
       // loaded together: an empty asm takes 16 values at a time (short of
       // registers the compiler otherwise waits for each load in turn)
       os << ind << "long long pq = ptc;\n" << ind << "asm volatile(\"\" : \"+v\"(pq));\n";
@@ -1610,14 +996,9 @@ struct Emitter {
         for (size_t i = i0; i < std::min(ms.size(), i0 + 16); ++i) os << (i > i0 ? ", " : " ") << "\"+v\"(" << ms[i] << ")";
         os << ");\n";
       }
-    } else if (mom_src == 0) {
+    } else {
       os << ind << "long long pq = ptc;\n" << ind << "asm volatile(\"\" : \"+v\"(pq));\n";
       load_momenta("mom", "N", "pq");
-    } else {
-      for (int p = 0; p < pr.npart; ++p)
-        for (int mu = 0; mu < 4; ++mu)
-          os << ind << "double m" << p << "_" << mu << " = M" << p << "_" << mu << "; asm volatile(\"\" : \"+v\"(m" << p
-             << "_" << mu << "));\n";
     }
   }
 
@@ -1884,353 +1265,6 @@ std::string emit_eval_kernel(const Dag& d, const Variant& v, const std::string& 
   e.st.lines = std::count(src.begin(), src.end(), '\n');
   if (stats) *stats = e.st;
   return src;
-}
-
-std::string emit_grad_kernel(const Dag& d, const Variant& v, const std::string& kname, EmitStats* stats) {
-  check_variant(d, v);
-  if (v.mode != HEL_SUM || v.prec != PREC_F64 || !(v.order & 4) || (v.order & 16) || d.distributed)
-    throw std::invalid_argument("gradient kernels take SUM, FP64, local blocks, the node-reduced graph");
-  Emitter e(d, v);
-  e.mom_src = 1;
-  const Process& pr = d.proc;
-  const int LB = popc(v.lane_mask), G = 1 << LB;
-  const int NF = pr.n_out + 1;
-  std::ostringstream& os = e.os;
-  os << "extern \"C\" __global__ void __launch_bounds__(" << v.block;
-  if (v.min_waves > 0) os << ", " << v.min_waves;
-  os << ")\n" << kname
-     << "(const double* __restrict__ u, double sqrt_s, long long N, double* __restrict__ logm2, double* __restrict__ "
-        "grad)\n{\n";
-  os << "  const long long gid = (long long)blockIdx.x * " << v.block << " + threadIdx.x;\n";
-  os << "  const long long pt = gid >> " << LB << ";\n";
-  os << "  const unsigned sub = (unsigned)(gid & " << (G - 1) << ");\n";
-  os << "  const long long ptc = pt < N ? pt : N - 1;\n";
-  for (int p = 0; p < pr.npart; ++p) os << "  double M" << p << "_0, M" << p << "_1, M" << p << "_2, M" << p << "_3;\n";
-  os << "  {\n    double uu[" << 4 * NF << "];\n";
-  os << "    for (int r = 0; r < " << 4 * NF << "; ++r) uu[r] = u[r * N + ptc];\n";
-  os << "    qx::RamboState<" << NF << "> S;\n    qx::rambo_forward<" << NF << ">(uu, sqrt_s, 1.0, S);\n";
-  os << "    double pin[4], kin[4];\n    qx::incoming_cm(sqrt_s, 1.0, pin, kin);\n";
-  for (int mu = 0; mu < 4; ++mu) os << "    M0_" << mu << " = pin[" << mu << "]; M1_" << mu << " = kin[" << mu << "];\n";
-  for (int j = 0; j < NF; ++j)
-    for (int mu = 0; mu < 4; ++mu) os << "    M" << (2 + j) << "_" << mu << " = S.k[" << j << "][" << mu << "];\n";
-  os << "  }\n";
-  // Helicity bits: lane bits from the lane index, enumerated bits inside the
-  // graph, loop bits by a run-time loop.  With loop bits the forward graph
-  // runs twice: once over all iterations for |M|^2, then again per iteration
-  // for the amplitudes that seed that iteration's adjoint sweep (recomputed,
-  // not stored).
-  const int nloop = popc(v.loop_mask);
-  os << "  const unsigned hrt = " << Emitter::deposit("sub", v.lane_mask) << ";\n";
-  os << "  double acc = 0.0;\n";
-  std::map<uint32_t, std::vector<int>> part;
-  std::vector<uint32_t> order;
-  e.partitions(part, order);
-  std::vector<int> sums = e.sum_nodes();
-  auto seeds_and_adjoint = [&]() {
-    for (size_t a = 0; a < sums.size(); ++a)
-      os << e.ind << "const qx::cx<double> c" << a << " = {A" << a << ".r * iM2, -A" << a << ".i * iM2};\n";
-    for (uint32_t key : order) e.grad_block(key, part[key]);
-  };
-  auto gm_init = [&]() {
-    for (int p = 2; p < pr.npart; ++p)
-      for (int mu = 0; mu < 4; ++mu) os << "  double gm" << p << "_" << mu << " = 0.0;\n";
-  };
-  auto reduce_acc = [&]() {
-    for (int o = 1; o < G; o <<= 1) os << "  acc += __shfl_xor(acc, " << o << ");\n";
-    os << "  const double iM2 = 1.0 / acc;\n";
-  };
-  if (nloop == 0) {
-    os << "  const unsigned hc = hrt;\n";
-    e.body();
-    reduce_acc();
-    gm_init();
-    seeds_and_adjoint();
-  } else {
-    const std::string loop_head = "  #pragma unroll 1\n  for (unsigned lp = 0; lp < " + std::to_string(1u << nloop) +
-                                  "u; ++lp) {\n    const unsigned hc = hrt | " + Emitter::deposit("lp", v.loop_mask) +
-                                  ";\n";
-    const std::string ind0 = e.ind;
-    os << loop_head;
-    e.ind = "    ";
-    e.body();
-    e.ind = ind0;
-    os << "  }\n";
-    reduce_acc();
-    gm_init();
-    os << loop_head;
-    e.ind = "    ";
-    os << e.ind << "double acc = 0.0;\n";  // |A|^2 of the recomputed pass, unused
-    e.body();
-    os << e.ind << "(void)acc;\n";
-    seeds_and_adjoint();
-    e.ind = ind0;
-    os << "  }\n";
-  }
-  for (int p = 2; p < pr.npart; ++p)
-    for (int mu = 0; mu < 4; ++mu)
-      for (int o = 1; o < G; o <<= 1) os << "  gm" << p << "_" << mu << " += __shfl_xor(gm" << p << "_" << mu << ", " << o << ");\n";
-  os << "  {\n    double uu[" << 4 * NF << "];\n";
-  os << "    for (int r = 0; r < " << 4 * NF << "; ++r) uu[r] = u[r * N + ptc];\n";
-  os << "    qx::RamboState<" << NF << "> S;\n    qx::rambo_forward<" << NF << ">(uu, sqrt_s, 1.0, S);\n";
-  os << "    double gk[" << NF << "][4] = {";
-  for (int j = 0; j < NF; ++j) {
-    os << (j ? ", " : "") << "{";
-    for (int mu = 0; mu < 4; ++mu) os << (mu ? ", " : "") << "gm" << (2 + j) << "_" << mu;
-    os << "}";
-  }
-  os << "};\n";
-  os << "    double gu[" << 4 * NF << "];\n    for (int r = 0; r < " << 4 * NF << "; ++r) gu[r] = 0.0;\n";
-  os << "    qx::rambo_vjp<" << NF << ">(uu, sqrt_s, 1.0, S, gk, gu);\n";
-  os << "    if (pt < N && sub == 0u) {\n      logm2[pt] = log(acc);\n";
-  os << "      for (int r = 0; r < " << 4 * NF << "; ++r) grad[r * N + pt] = gu[r];\n    }\n  }\n}\n";
-  e.st.flops_per_point *= (double)G * (double)(1 << popc(v.loop_mask));
-  if (stats) *stats = e.st;
-  return os.str();
-}
-
-// ---------------------------------------------------------------------------
-// Split gradient: amplitude kernel + one adjoint kernel per photon partition
-// ---------------------------------------------------------------------------
-std::string emit_amp_kernel(const Dag& d, const Variant& v, const std::string& kname, EmitStats* stats) {
-  check_variant(d, v);
-  if (v.mode != HEL_SUM || v.prec != PREC_F64 || (v.order & (8 | 16)) || d.distributed)
-    throw std::invalid_argument("amplitude kernels take SUM, FP64, the node-reduced graph, no loop or LDS schedule");
-  Emitter e(d, v);
-  e.amp_store = true;
-  e.batch_mom = (v.order & 8192) != 0;
-  if (v.order & 2048) {
-    e.coop = true;
-    e.build_twins();
-  }
-  const Process& pr = d.proc;
-  const int LB = popc(v.lane_mask), G = 1 << LB;
-  std::ostringstream& os = e.os;
-  os << "extern \"C\" __global__ void __launch_bounds__(" << v.block << ")\n" << kname
-     << "(const double* __restrict__ mom, long long N, double* __restrict__ amp, double* __restrict__ logm2, "
-        "double* __restrict__ im2)\n{\n";
-  os << "  const long long gid = (long long)blockIdx.x * " << v.block << " + threadIdx.x;\n";
-  os << "  const long long pt = gid >> " << LB << ";\n";
-  os << "  const unsigned sub = (unsigned)(gid & " << (G - 1) << ");\n";
-  os << "  const long long ptc = pt < N ? pt : N - 1;\n";
-  {
-    // per-lane staging of one iteration's amplitudes
-    Emitter probe(d, v);
-    os << "  __shared__ double qx_as[" << 2 * probe.sum_nodes().size() * v.block << "];\n";
-  }
-  if (!e.local()) e.load_momenta("mom", "N", "ptc");
-  os << "  double acc = 0.0;\n";
-  e.lane_work(Emitter::deposit("sub", v.lane_mask));
-  for (int o = 1; o < G; o <<= 1) os << "  acc += __shfl_xor(acc, " << o << ");\n";
-  os << "  if (pt < N && sub == 0u) { logm2[pt] = log(acc); im2[pt] = 1.0 / acc; }\n}\n";
-  e.st.flops_per_point *= (double)G * (double)(1 << popc(v.loop_mask));
-  if (stats) *stats = e.st;
-  return os.str();
-}
-
-std::vector<std::pair<uint32_t, int>> adjoint_walks(const Dag& d, const Variant& v) {
-  std::map<uint32_t, std::vector<int>> part;
-  std::vector<uint32_t> order;
-  Emitter probe(d, v);
-  probe.partitions(part, order);
-  std::vector<std::pair<uint32_t, int>> w;
-  for (uint32_t key : order) {
-    bool split = false;
-    if (!d.distributed) {
-      Emitter pe(d, v);
-      std::vector<int> ps = pe.sum_nodes();
-      for (size_t a = 0; a < ps.size(); ++a) pe.acc_of_sum[ps[a]] = (int)a;
-      pe.collect_block(part[key]);
-      split = pe.factor_block(part[key]);
-    }
-    if (split) {
-      w.push_back({key, 1});
-      w.push_back({key, 2});
-    } else {
-      w.push_back({key, 0});
-    }
-  }
-  return w;
-}
-
-std::string emit_partition_adjoint_kernels(const Dag& d, const Variant& v, const std::string& kprefix, int* count,
-                                           EmitStats* stats, uint32_t only_key, int only_phase, int t0) {
-  check_variant(d, v);
-  if (v.mode != HEL_SUM || v.prec != PREC_F64 || !(v.order & 4) || (v.order & (8 | 16)))
-    throw std::invalid_argument("adjoint kernels take SUM, FP64, local blocks");
-  if (d.distributed && v.enum_mask)
-    throw std::invalid_argument("adjoint kernels of the distributed graph take one configuration per iteration");
-  const Process& pr = d.proc;
-  const int LB = popc(v.lane_mask), G = 1 << LB;
-  const int nloop = popc(v.loop_mask);
-  std::map<uint32_t, std::vector<int>> part;
-  std::vector<uint32_t> order;
-  {
-    Emitter probe(d, v);
-    probe.partitions(part, order);
-  }
-  std::ostringstream all;
-  EmitStats tot;
-  int t = t0;
-  // per-lane LDS of one workgroup at one wave per SIMD (160 KB per CU)
-  const int64_t kLdsBytes = 160 * 1024;
-  for (uint32_t key : order) {
-    if (only_key != ~0u && key != only_key) continue;
-    // factored partitions: two kernels (e-_out-side walk, e-_in-side walk)
-    bool split = false;
-    if (!d.distributed) {
-      Emitter pe(d, v);
-      std::vector<int> ps = pe.sum_nodes();
-      for (size_t a = 0; a < ps.size(); ++a) pe.acc_of_sum[ps[a]] = (int)a;
-      pe.collect_block(part[key]);
-      split = pe.factor_block(part[key]);
-    }
-    for (int phase = split ? 1 : 0; phase <= (split ? 2 : 0); ++phase) {
-    if (only_phase >= 0 && phase != only_phase) continue;
-    // the split walks keep their polarisation gradients in LDS when they fit
-    // beside the momentum and propagator gradients
-    for (int ge_lds = phase >= 1 ? 1 : 0; ge_lds >= 0; --ge_lds) {
-    Emitter e(d, v);
-    e.grad_phase = phase;
-    e.ge_in_lds = ge_lds != 0;
-    e.lds_atomic = phase == 1;
-    e.mom_src = 0;       // momenta reloaded per block from the workspace
-    e.gm_in_lds = true;  // gradient accumulators in per-lane LDS slots
-    e.gq_in_lds = !d.distributed;  // propagator gradients per propagator, flushed once
-    std::vector<int> sums = e.sum_nodes();
-    for (size_t a = 0; a < sums.size(); ++a) e.acc_of_sum[sums[a]] = (int)a;
-    std::ostringstream& os = e.os;
-    os << "extern \"C\" __global__ void __launch_bounds__(" << v.block << ")\n" << kprefix << "_" << t
-       << "(const double* __restrict__ mom, const double* __restrict__ amp, const double* __restrict__ im2, "
-          "long long N, double* __restrict__ gm)\n{\n";
-    const int ngm = 4 * (pr.npart - pr.i_eout);
-    os << "  __shared__ double qx_gm[" << ngm * v.block << "];\n";
-    const std::string gq_mark = "  //@GQ@\n";
-    os << gq_mark;
-    os << "  const long long gid = (long long)blockIdx.x * " << v.block << " + threadIdx.x;\n";
-    os << "  const long long pt = gid >> " << LB << ";\n";
-    os << "  const unsigned sub = (unsigned)(gid & " << (G - 1) << ");\n";
-    os << "  const long long ptc = pt < N ? pt : N - 1;\n";
-    os << "  const long long NL = N * " << G << ";\n  const long long gidc = gid < NL ? gid : NL - 1;\n";
-    for (int p = pr.i_eout; p < pr.npart; ++p)
-      for (int mu = 0; mu < 4; ++mu) os << "  " << e.gmref(p, mu) << " = 0.0;\n";
-    const std::string gq_zero_mark = "  //@GQZERO@\n";
-    os << gq_zero_mark;
-    os << "  const double iM2 = im2[ptc];\n";
-    os << "  const unsigned hrt = " << Emitter::deposit("sub", v.lane_mask) << ";\n";
-    // merge: the walked side (phase 1: e-_out, phase 2: e-_in) holds no
-    // looped photon
-    uint32_t in_side = 0;
-    for (int a = 0; a < pr.P; ++a)
-      if ((key >> a) & 1) in_side |= 1u << pr.photon_particle[a];
-    const uint32_t photons_all = ((1u << pr.npart) - 1) & ~(1u << pr.i_ein) & ~(1u << pr.i_eout);
-    const uint32_t walked = phase == 1 ? (photons_all & ~in_side) : phase == 2 ? in_side : photons_all;
-    const bool merge = split && nloop > 0 && (v.loop_mask & walked) == 0;
-    if (merge) {
-      Emitter pm(d, v);
-      std::vector<int> ps = pm.sum_nodes();
-      for (size_t a = 0; a < ps.size(); ++a) pm.acc_of_sum[ps[a]] = (int)a;
-      pm.collect_block(part[key]);
-      pm.factor_block(part[key]);
-      std::set<uint32_t> pats;
-      for (auto& kv : (phase == 1 ? pm.memB : pm.memJ)) pats.insert(kv.second);
-      for (uint32_t q : pats)
-        os << "  qx::sp4<double> " << (phase == 1 ? "T" : "W") << q << " = qx::zero4<double>();\n";
-    }
-    os << "  #pragma unroll 1\n  for (unsigned lp = 0; lp < " << (1u << nloop) << "u; ++lp) {\n";
-    os << "    const unsigned hc = hrt | " << Emitter::deposit("lp", v.loop_mask) << ";\n";
-    e.ind = "    ";
-    // seeds: conj(A_h) / |M|^2 of this iteration's configurations, loaded
-    // where the block first needs them (after its leaf-sum walk), 8 at a
-    // time behind an empty asm that takes all 16 values at once (otherwise,
-    // short of registers, the compiler waits for each load before issuing
-    // the next)
-    {
-      std::ostringstream sc;
-      const size_t kBatch = 8;
-      for (size_t a0 = 0; a0 < sums.size(); a0 += kBatch) {
-        const size_t a1 = std::min(sums.size(), a0 + kBatch);
-        for (size_t a = a0; a < a1; ++a)
-          sc << "const unsigned h" << a << " = hc | " << d.nodes[sums[a]].cfg << "u; double cr" << a << " = amp[(2 * h"
-             << a << ") * N + ptc], ci" << a << " = amp[(2 * h" << a << " + 1) * N + ptc];\n";
-        sc << "asm volatile(\"\" :";
-        for (size_t a = a0; a < a1; ++a) sc << (a > a0 ? ", " : " ") << "\"+v\"(cr" << a << "), \"+v\"(ci" << a << ")";
-        sc << ");\n";
-        for (size_t a = a0; a < a1; ++a)
-          sc << "const qx::cx<double> c" << a << " = {cr" << a << " * iM2, -ci" << a << " * iM2};\n";
-      }
-      e.seed_code = sc.str();
-    }
-    if (d.distributed)
-      e.dist_adjoint_block(key, part[key]);
-    else {
-      e.merge_part = merge ? 1 : 0;
-      e.grad_block(key, part[key]);
-    }
-    e.ind = "  ";
-    os << "  }\n";
-    if (merge) {
-      os << "  {\n    const unsigned hc = hrt;\n";
-      e.ind = "    ";
-      e.merge_part = 2;
-      e.grad_block(key, part[key]);
-      e.merge_part = 0;
-      e.ind = "  ";
-      os << "  }\n";
-    }
-    if (!e.gq_slot.empty()) {
-      // propagator gradients of every iteration -> momentum gradients
-      os << "  {\n";
-      e.ind = "    ";
-      e.load_momenta("mom", "N", "ptc");
-      e.flush_gq();
-      e.ind = "  ";
-      os << "  }\n";
-    }
-    for (int p = pr.i_eout; p < pr.npart; ++p)
-      for (int mu = 0; mu < 4; ++mu) {
-        os << "  double gm" << p << "_" << mu << " = " << e.gmref(p, mu) << ";\n";
-        for (int o = 1; o < G; o <<= 1)
-          os << "  gm" << p << "_" << mu << " += __shfl_xor(gm" << p << "_" << mu << ", " << o << ");\n";
-      }
-    // all loads of gm before any store (the rows may alias for all the
-    // compiler knows, which would otherwise serialise each load-add-store)
-    os << "  if (pt < N && sub == 0u) {\n";
-    for (int p = pr.i_eout; p < pr.npart; ++p)
-      for (int mu = 0; mu < 4; ++mu)
-        os << "    const double o" << p << "_" << mu << " = gm[" << (4 * p + mu) << " * N + pt];\n";
-    for (int p = pr.i_eout; p < pr.npart; ++p)
-      for (int mu = 0; mu < 4; ++mu)
-        os << "    gm[" << (4 * p + mu) << " * N + pt] = o" << p << "_" << mu << " + gm" << p << "_" << mu << ";\n";
-    os << "  }\n}\n";
-    const int ns = (int)e.gq_slot.size(), nge = (int)e.ge_slot.size();
-    if (ge_lds && (int64_t)(ngm + 5 * ns + 3 * nge) * v.block * 8 > kLdsBytes) continue;  // registers instead
-    tot.flops_per_point += e.st.flops_per_point * (double)G * (double)(1 << nloop);
-    std::string ks = os.str();
-    {
-      std::string decl, zero, gezero;
-      if (ns > 0) {
-        decl = "  __shared__ double qx_gq[" + std::to_string(5 * ns * v.block) + "];\n";
-        for (int k = 0; k < ns; ++k)
-          for (int c = 0; c < 5; ++c) zero += "  " + e.gqref(k, c) + " = 0.0;\n";
-      }
-      if (nge > 0) {
-        decl += "  __shared__ double qx_ge[" + std::to_string(3 * nge * v.block) + "];\n";
-        for (int k = 0; k < nge; ++k)
-          for (int c = 0; c < 3; ++c) gezero += "        " + e.geref(k, c) + " = 0.0;\n";
-      }
-      ks.replace(ks.find(gq_mark), gq_mark.size(), decl);
-      ks.replace(ks.find(gq_zero_mark), gq_zero_mark.size(), zero);
-      if (e.ge_in_lds) ks.replace(ks.find(e.ge_zero_mark), e.ge_zero_mark.size(), gezero);
-    }
-    all << ks;
-    ++t;
-    break;
-    }
-    }
-  }
-  if (count) *count = t - t0;
-  if (stats) *stats = tot;
-  return all.str();
 }
 
 std::string emit_body_function(const Dag& d, const Variant& v, const std::string& fname, EmitStats* stats,

@@ -3,7 +3,6 @@
 
 #include <cstdint>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "qedx_dag.hpp"
@@ -77,37 +76,6 @@ Dag graph_for(const Process& proc, const Variant& v, double* t_build, double* t_
 // marks and recomputes those points with the FP64 body of the same graph.
 // No memory beyond the caller's buffers is used.
 std::string emit_eval_kernel(const Dag& d, const Variant& v, const std::string& kname, EmitStats* st);
-
-// Gradient kernel (SUM mode, FP64, partition-local blocks, no loop bits):
-//   extern "C" __global__ void <kname>(const double* u, double sqrt_s,
-//                                      long long N, double* logm2, double* grad)
-// RAMBO forward, forward graph (log |M|^2), adjoint graph and adjoint RAMBO
-// in one kernel; u and grad are [4(n+1)][N].  No device header included:
-// the caller prepends it.
-std::string emit_grad_kernel(const Dag& d, const Variant& v, const std::string& kname, EmitStats* st);
-
-// Split gradient (SUM, FP64), for processes whose fused gradient kernel would
-// not fit the register file.  The amplitude kernel stores every
-// configuration's amplitude, log |M|^2 and 1/|M|^2:
-//   extern "C" __global__ void <kname>(const double* mom, long long N,
-//       double* amp /*[2H][N]*/, double* logm2, double* im2)
-std::string emit_amp_kernel(const Dag& d, const Variant& v, const std::string& kname, EmitStats* st);
-// Kernels <kprefix>_<t>, t = 0..*count-1, launched in order: per photon
-// partition the adjoint sweep for every configuration (seeds conj(A_h)/|M|^2
-// read from amp), adding its momentum gradient into gm.  A partition whose
-// dots factor into per-pattern leaf sums takes two kernels, the e-_out-side
-// walk and the e-_in-side walk, each obtaining the other side's leaf sums by
-// a forward walk of its own; others take one.
-//   extern "C" __global__ void <kprefix>_<t>(const double* mom, const double* amp,
-//       const double* im2, long long N, double* gm)
-// Only the kernels of partition only_key (~0u: all) and walk only_phase
-// (-1: all; 0 = the one-kernel sweep, 1 = e-_out side, 2 = e-_in side) are
-// emitted, numbered from t0; *count is the number emitted.
-std::string emit_partition_adjoint_kernels(const Dag& d, const Variant& v, const std::string& kprefix, int* count,
-                                           EmitStats* st, uint32_t only_key = ~0u, int only_phase = -1, int t0 = 0);
-// The (partition, walk) pairs of the adjoint kernels of (d, v) in launch
-// order: (key, 1) and (key, 2) for a factored partition, (key, 0) otherwise.
-std::vector<std::pair<uint32_t, int>> adjoint_walks(const Dag& d, const Variant& v);
 
 // Device function text of one process body (used by the mixed batch module):
 //   __device__ double <fname>(const double* mom, long long N, long long pt,

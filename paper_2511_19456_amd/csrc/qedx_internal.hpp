@@ -32,12 +32,11 @@ struct qed_process {
   hipModule_t mod_aux = nullptr;  // RAMBO and gradient kernels
   hipFunction_t f_rambo = nullptr;
   hipFunction_t f_grad = nullptr;
-  int grad_block = 256;
-  int grad_lanes = 0;
+  int grad_points = 0;  // points of one wave of the gradient kernel
+  int max_waves = 0;    // waves the device holds at two per SIMD
   // split gradient (n = 4): kernels; the workspace is the caller's
-  int grad_split = 0, amp_lanes = 0, adj_lanes = 0;
-  hipFunction_t f_grambo = nullptr, f_gamp = nullptr, f_grvjp = nullptr;
-  std::vector<hipFunction_t> f_gadj;
+  int grad_split = 0;
+  hipFunction_t f_grambo = nullptr, f_gmom = nullptr, f_grvjp = nullptr;
   std::string eval_src;
   ~qed_process() {
     // launches are asynchronous: wait for any still running before the

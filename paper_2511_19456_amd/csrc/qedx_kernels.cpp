@@ -1,26 +1,11 @@
 // qedx_kernels.cpp -- auxiliary generated module (RAMBO; gradient).
 #include "qedx_kernels.hpp"
 
+#include "qedx_coop.hpp"
+
 #include <sstream>
 
 namespace qedx {
-
-Variant grad_variant(const Process& proc) {
-  Variant g;
-  g.prec = PREC_F64;
-  g.mode = HEL_SUM;
-  g.order = 4;
-  g.block = 256;
-  g.split = proc.P / 2;
-  g.join_side = 1;
-  uint32_t all = (1u << proc.npart) - 1;
-  g.enum_mask = 0;
-  if (proc.npart > 6) g.enum_mask |= 1u << proc.i_eout;
-  if (proc.npart > 7) g.enum_mask |= 1u << proc.i_ein;
-  g.lane_mask = all & ~g.enum_mask;
-  g.loop_mask = 0;
-  return g;
-}
 
 std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInfo* info) {
   std::ostringstream os;
@@ -42,21 +27,22 @@ std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInf
   os << "#pragma unroll\n  for (int d = 0; d < 4; ++d) { mom[d * N + pt] = pin[d]; mom[(4 + d) * N + pt] = kin[d]; }\n";
   os << "#pragma unroll\n  for (int j = 0; j < " << NF << "; ++j)\n#pragma unroll\n    for (int d = 0; d < 4; ++d) mom[(4 * (2 + j) + d) * N + pt] = S.k[j][d];\n";
   os << "}\n";
-  if (v.mode == HEL_SUM && v.prec == PREC_F64 && n <= 3) {
-    // fused: RAMBO, forward graph, adjoint graph and RAMBO adjoint in one kernel
-    Variant g = grad_variant(proc);
-    Dag d = graph_for(proc, g, nullptr, nullptr);
-    EmitStats st;
-    os << emit_grad_kernel(d, g, "qedx_grad_n" + ns, &st);
-    ai.grad_lanes = 1 << __builtin_popcount(g.lane_mask);
-    ai.grad_block = g.block;
-  } else if (v.mode == HEL_SUM && v.prec == PREC_F64 && n == 4) {
-    // split: RAMBO into a workspace, amplitudes of every configuration, one
-    // adjoint kernel per photon partition, RAMBO adjoint
+  if (v.mode != HEL_SUM || v.prec != PREC_F64 || n > 4) {
+    if (info) *info = ai;
+    return os.str();
+  }
+  os << subset_header_text() << "\n";
+  EmitStats st;
+  ai.grad_points = 64 / coop_grad_lanes(proc);
+  if (n <= 3) {
+    // fused: RAMBO, currents, reverse sweep and RAMBO adjoint in one kernel
+    os << emit_coop_grad_kernel(proc, "qedx_grad_n" + ns, true, &st);
+  } else {
+    // split: RAMBO into the workspace, the gradient over its momenta, RAMBO adjoint
     ai.split = 1;
+    os << emit_coop_grad_kernel(proc, "qedx_gmom_n" + ns, false, &st);
     os << "extern \"C\" __global__ void __launch_bounds__(256)\nqedx_grambo_n" << n
-       << "(const double* __restrict__ u, long long ldu, double sqrt_s, long long N, double* __restrict__ mom, "
-          "double* __restrict__ gm)\n{\n";
+       << "(const double* __restrict__ u, long long ldu, double sqrt_s, long long N, double* __restrict__ mom)\n{\n";
     os << "  const long long pt = (long long)blockIdx.x * 256 + threadIdx.x;\n";
     os << "  if (pt >= N) return;\n";
     os << "  double uu[" << 4 * NF << "];\n";
@@ -66,8 +52,6 @@ std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInf
     os << "  double pin[4], kin[4];\n  qx::incoming_cm(sqrt_s, 1.0, pin, kin);\n";
     os << "#pragma unroll\n  for (int d = 0; d < 4; ++d) { mom[d * N + pt] = pin[d]; mom[(4 + d) * N + pt] = kin[d]; }\n";
     os << "#pragma unroll\n  for (int j = 0; j < " << NF << "; ++j)\n#pragma unroll\n    for (int d = 0; d < 4; ++d) mom[(4 * (2 + j) + d) * N + pt] = S.k[j][d];\n";
-    // the final-state momentum-gradient rows the adjoint kernels add into
-    os << "#pragma unroll\n  for (int r = 8; r < " << 4 * (NF + 2) << "; ++r) gm[r * N + pt] = 0.0;\n";
     os << "}\n";
     os << "extern \"C\" __global__ void __launch_bounds__(256)\nqedx_grvjp_n" << n
        << "(const double* __restrict__ u, long long ldu, double sqrt_s, long long N, const double* __restrict__ gm, "
@@ -84,93 +68,6 @@ std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInf
     os << "  qx::rambo_vjp<" << NF << ">(uu, sqrt_s, 1.0, S, gk, gu);\n";
     os << "#pragma unroll\n  for (int r = 0; r < " << 4 * NF << "; ++r) grad[r * ldg + pt] = gu[r];\n";
     os << "}\n";
-    // amplitudes: the e-_out spin over 2 lanes, the e-_in spin and up to 3
-    // photon bits in the graph, the rest looped, partition-local blocks (the
-    // shape of the 5-photon helicity-sum eval kernel)
-    const uint32_t all = (1u << proc.npart) - 1;
-    Variant a;
-    a.prec = PREC_F64;
-    a.mode = HEL_SUM;
-    // the two lanes of a point share the e-_in side; block momenta loaded
-    // together (3.11 against 3.43 ms per 2^17 points)
-    a.order = 4 | 2048 | 8192;
-    a.block = 256;
-    a.split = proc.P / 2;
-    a.join_side = 1;
-    a.lane_mask = 1u << proc.i_eout;
-    const uint32_t photons = all & ~(1u << proc.i_ein) & ~(1u << proc.i_eout);
-    a.enum_mask = 1u << proc.i_ein;
-    int k = 0;
-    for (int b = 0; b < proc.npart && k < 3; ++b)
-      if ((photons >> b) & 1) {
-        a.enum_mask |= 1u << b;
-        ++k;
-      }
-    a.loop_mask = photons & ~a.enum_mask;
-    {
-      Dag d = graph_for(proc, a, nullptr, nullptr);
-      EmitStats st;
-      os << emit_amp_kernel(d, a, "qedx_gamp_n" + ns, &st);
-    }
-    ai.amp_lanes = 1 << __builtin_popcount(a.lane_mask);
-    // adjoint: the e-_out spin over 2 lanes, the e-_in spin and every photon
-    // polarisation but the last enumerated in the graph (currents and
-    // adjoints that do not depend on a bit serve every configuration it
-    // enumerates; the factored partition adjoint keeps only per-pattern
-    // current sums across a walk), the last photon looped, one kernel per
-    // partition.  Measured at n = 4 (2^18 points, whole gradient): 2, 4, 8,
-    // 16, 32, 64 configurations in the graph 105, 54, 50, 45, 41, 58 ms
-    Variant g = a;
-    g.order = 4;
-    g.lane_mask = 1u << proc.i_eout;
-    g.enum_mask = 1u << proc.i_ein;
-    for (int b = 0; b + 1 < proc.P; ++b) g.enum_mask |= 1u << proc.photon_particle[b];
-    g.loop_mask = all & ~g.enum_mask & ~g.lane_mask;
-    if (v.rewrite) {
-      // the subset-current sweep of distributed graphs takes one configuration
-      // per iteration: both spins on lanes, every photon looped
-      g.lane_mask = (1u << proc.i_ein) | (1u << proc.i_eout);
-      g.enum_mask = 0;
-      g.loop_mask = photons;
-    }
-    // the sweep follows the process's graph form: node-reduced prefix tries
-    // (default; measured faster at n = 4: the trie walk holds only its path)
-    // or, for rewrite = 1 processes, the subset currents swept top-down
-    g.rewrite = v.rewrite;
-    {
-      Dag d = graph_for(proc, g, nullptr, nullptr);
-      if (v.rewrite) {
-        EmitStats st;
-        os << emit_partition_adjoint_kernels(d, g, "qedx_gadj_n" + ns, &ai.n_adj, &st);
-      } else {
-        // Each walk of a factored partition loops a photon of the side it
-        // does not walk (one kernel per walk, each with its own graph): the
-        // walked side's currents then do not depend on the loop and it is
-        // walked once with its seeds summed over the iterations.  Other
-        // partitions keep the last photon looped.
-        int t = 0;
-        for (auto& w : adjoint_walks(d, g)) {
-          Variant gk = g;
-          if (w.second != 0) {
-            uint32_t in_side = 0;
-            for (int a = 0; a < proc.P; ++a)
-              if ((w.first >> a) & 1) in_side |= 1u << proc.photon_particle[a];
-            const uint32_t other = w.second == 1 ? in_side : (photons & ~in_side);
-            if (other) {
-              gk.loop_mask = other & (~other + 1u);  // lowest photon of that side
-              gk.enum_mask = all & ~gk.lane_mask & ~gk.loop_mask;
-            }
-          }
-          Dag dk = graph_for(proc, gk, nullptr, nullptr);
-          EmitStats st;
-          int c = 0;
-          os << emit_partition_adjoint_kernels(dk, gk, "qedx_gadj_n" + ns, &c, &st, w.first, w.second, t);
-          t += c;
-        }
-        ai.n_adj = t;
-      }
-    }
-    ai.adj_lanes = 1 << __builtin_popcount(g.lane_mask);
   }
   if (info) *info = ai;
   return os.str();

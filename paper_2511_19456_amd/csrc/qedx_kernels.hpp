@@ -10,30 +10,22 @@ namespace qedx {
 
 // Launch shapes of the auxiliary module's gradient kernels.
 struct AuxInfo {
-  int grad_lanes = 0, grad_block = 0;  // fused gradient kernel (0 if none)
-  int split = 0;                       // 1: split gradient kernels instead
-  int n_adj = 0;                       // number of per-partition adjoint kernels
-  int amp_lanes = 0, adj_lanes = 0;    // lanes per point of the amplitude / adjoint kernels
+  int grad_points = 0;  // points of one wave of the gradient kernel (0: no gradient)
+  int split = 0;        // 1: split gradient kernels
 };
 
 // HIP source with
 //   qedx_rambo_n<n>(const double* u, double sqrt_s, long long N, double* mom)
-// and, for SUM-mode FP64 processes, the gradient of log |M|^2 with respect to
-// the RAMBO uniforms:
+// and, for SUM-mode FP64 processes of n <= 4, the gradient of log |M|^2 with
+// respect to the RAMBO uniforms:
 //  - n <= 3, fused: qedx_grad_n<n>(const double* u, double sqrt_s, long long N,
-//      double* logm2, double* grad);
-//  - n = 4, split over a caller workspace (the fused kernel spills heavily):
-//      qedx_grambo_n<n>(u, ldu, sqrt_s, N, mom, gm)  RAMBO into the workspace,
-//          the final-state momentum-gradient rows of gm zeroed,
-//      qedx_gamp_n<n>(mom, N, amp, logm2, im2)  amplitudes of every configuration,
-//      qedx_gadj_n<n>_<t>(mom, amp, im2, N, gm)  adjoint of photon partition t,
+//      double* logm2, double* grad, int tiles);
+//  - n = 4, split over a caller workspace (two points per wave leave no LDS for
+//      the phase space of a whole wave's points):
+//      qedx_grambo_n<n>(u, ldu, sqrt_s, N, mom)      RAMBO into the workspace,
+//      qedx_gmom_n<n>(mom, N, gm, logm2)             momentum gradient of log |M|^2,
 //      qedx_grvjp_n<n>(u, ldu, sqrt_s, N, gm, grad, ldg)  RAMBO adjoint.
-// n >= 5 has RAMBO only (its split gradient module takes tens of minutes of
-// compile time and is not built).
+// n >= 5 has RAMBO only.
 std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInfo* info);
-
-// Kernel shape of the fused gradient (n <= 3): every photon polarisation and
-// as many electron spins as fit on 64 lanes; the rest enumerated in the graph.
-Variant grad_variant(const Process& proc);
 
 }  // namespace qedx

@@ -564,12 +564,10 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   auto t0 = std::chrono::steady_clock::now();
   HIPCHK(hipModuleLoadData(&p->mod, co.data()));
   HIPCHK(hipModuleGetFunction(&p->f_eval, p->mod, p->info.kernel_name));
-  if (prec == QED_FP64 && pair_kernel(p->proc, p->var) && pair_persistent(p->proc)) {
-    int dev = 0, ncu = 256;
-    HIPCHK(hipGetDevice(&dev));
-    HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    p->max_groups = ncu;
-  }
+  int dev = 0, ncu = 256;
+  HIPCHK(hipGetDevice(&dev));
+  HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+  if (prec == QED_FP64 && pair_kernel(p->proc, p->var) && pair_persistent(p->proc)) p->max_groups = ncu;
   if (p->var.fixup) {
     std::string fx = std::string(p->info.kernel_name) + "_fix";
     HIPCHK(hipModuleGetFunction(&p->f_fix, p->mod, fx.c_str()));
@@ -584,12 +582,8 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   try {
     AuxInfo ai;
     asrc = emit_aux_module(p->proc, p->var, n, &ai);
-    p->grad_lanes = ai.grad_lanes;
-    p->grad_block = ai.grad_block ? ai.grad_block : 256;
+    p->grad_points = ai.grad_points;
     p->grad_split = ai.split;
-    p->amp_lanes = ai.amp_lanes;
-    p->adj_lanes = ai.adj_lanes;
-    p->f_gadj.assign(ai.n_adj, nullptr);
   } catch (const std::exception& e) {
     return fail(QED_ERR_INVALID_ARG, std::string("aux emit: ") + e.what());
   }
@@ -606,11 +600,10 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   if (hipModuleGetFunction(&p->f_grad, p->mod_aux, ("qedx_grad_n" + ns).c_str()) != hipSuccess) p->f_grad = nullptr;
   if (p->grad_split) {
     HIPCHK(hipModuleGetFunction(&p->f_grambo, p->mod_aux, ("qedx_grambo_n" + ns).c_str()));
-    HIPCHK(hipModuleGetFunction(&p->f_gamp, p->mod_aux, ("qedx_gamp_n" + ns).c_str()));
+    HIPCHK(hipModuleGetFunction(&p->f_gmom, p->mod_aux, ("qedx_gmom_n" + ns).c_str()));
     HIPCHK(hipModuleGetFunction(&p->f_grvjp, p->mod_aux, ("qedx_grvjp_n" + ns).c_str()));
-    for (size_t t = 0; t < p->f_gadj.size(); ++t)
-      HIPCHK(hipModuleGetFunction(&p->f_gadj[t], p->mod_aux, ("qedx_gadj_n" + ns + "_" + std::to_string(t)).c_str()));
   }
+  p->max_waves = 8 * ncu;
   (void)hipGetLastError();
   p->info.create_ms_load = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   *out = p.release();
@@ -687,14 +680,15 @@ extern "C" qed_status qed_rambo(const qed_process* p, const double* uniforms, do
   return launch(p->f_rambo, N, 256, stream, args);
 }
 
-// Split gradient: bytes of workspace per point (momenta and momentum
-// gradient [4 npart] each, amplitudes [2 H], 1/|M|^2) and the largest chunk
-// of points one pass takes (a power of two, at most 2^20 and 512 MB).
+// Split gradient: bytes of workspace per point that a caller provides and the
+// largest chunk of points one pass takes (a power of two, at most 2^20 and 512
+// MB).  The kernels use less: momenta and momentum gradients, [4 npart] each.
 static int64_t grad_ws_per_point(const qed_process* p) {
   const int npart = p->n + p->n_in + 2;
   const int64_t H = (int64_t)1 << npart;
   return 8 * (2 * 4 * (int64_t)npart + 2 * H + 1);
 }
+static int64_t grad_used_per_point(const qed_process* p) { return 8 * 2 * 4 * (int64_t)(p->n + p->n_in + 2); }
 
 static int64_t grad_max_chunk(const qed_process* p) {
   int64_t C = (int64_t)1 << 20;
@@ -715,26 +709,19 @@ extern "C" qed_status qed_eval_grad_workspace_size(const qed_process* p, int64_t
 static qed_status grad_split_chunks(const qed_process* p, const double* uniforms, double sqrt_s, int64_t N,
                                     double* out_logm2, double* out_grad, double* ws, int64_t C, void* stream) {
   const int npart = p->n + p->n_in + 2;
-  const int64_t H = (int64_t)1 << npart;
   for (int64_t off = 0; off < N; off += C) {
     long long cnt = (long long)std::min<int64_t>(C, N - off);
     long long ldu = (long long)N;
     double* mom = ws;
     double* gm = mom + 4 * (int64_t)npart * cnt;
-    double* amp = gm + 4 * (int64_t)npart * cnt;
-    double* im2 = amp + 2 * H * cnt;
     const double* u = uniforms + off;
     double* lg = out_logm2 + off;
     double* gr = out_grad + off;
     qed_status st;
-    void* a1[] = {(void*)&u, (void*)&ldu, (void*)&sqrt_s, (void*)&cnt, (void*)&mom, (void*)&gm};
+    void* a1[] = {(void*)&u, (void*)&ldu, (void*)&sqrt_s, (void*)&cnt, (void*)&mom};
     if ((st = launch(p->f_grambo, cnt, 256, stream, a1))) return st;
-    void* a2[] = {(void*)&mom, (void*)&cnt, (void*)&amp, (void*)&lg, (void*)&im2};
-    if ((st = launch(p->f_gamp, cnt * (int64_t)p->amp_lanes, 256, stream, a2))) return st;
-    for (hipFunction_t f : p->f_gadj) {
-      void* a3[] = {(void*)&mom, (void*)&amp, (void*)&im2, (void*)&cnt, (void*)&gm};
-      if ((st = launch(f, cnt * (int64_t)p->adj_lanes, 256, stream, a3))) return st;
-    }
+    void* a2[] = {(void*)&mom, (void*)&cnt, (void*)&gm, (void*)&lg};
+    if ((st = launch(p->f_gmom, cnt * (64 / p->grad_points), 64, stream, a2))) return st;
     void* a4[] = {(void*)&u, (void*)&ldu, (void*)&sqrt_s, (void*)&cnt, (void*)&gm, (void*)&gr, (void*)&ldu};
     if ((st = launch(p->f_grvjp, cnt, 256, stream, a4))) return st;
   }
@@ -767,7 +754,7 @@ extern "C" qed_status qed_eval_grad(const qed_process* p, const double* uniforms
     return fail(QED_ERR_INVALID_ARG, "workspace of at least " + std::to_string(need_min) +
                                          " bytes required (qed_eval_grad_workspace_size gives the full size)");
   if ((uintptr_t)workspace % 8) return fail(QED_ERR_INVALID_ARG, "workspace must be 8-byte aligned");
-  const int64_t C = std::min(N, std::min(workspace_bytes / per_pt, grad_max_chunk(p)));
+  const int64_t C = std::min(N, std::min<int64_t>(workspace_bytes / grad_used_per_point(p), (int64_t)1 << 20));
   return grad_split_chunks(p, uniforms, sqrt_s, N, out_logm2, out_grad, (double*)workspace, C, stream);
 }
 
@@ -788,7 +775,7 @@ extern "C" qed_status qed_eval_grad_noalloc(const qed_process* p, const double* 
   void* ws = nullptr;
   hipError_t e = qedx_rt::scratch_address(&ws);
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("scratch address: ") + hipGetErrorString(e));
-  const int64_t C = std::min(N, std::min(qedx_rt::kScratchBytes / per_pt, grad_max_chunk(p)));
+  const int64_t C = std::min(N, std::min<int64_t>(qedx_rt::kScratchBytes / grad_used_per_point(p), (int64_t)1 << 20));
   return grad_split_chunks(p, uniforms, sqrt_s, N, out_logm2, out_grad, (double*)ws, C, stream);
 }
 
@@ -913,8 +900,13 @@ std::string cache_dir() { return cache_dir_str(); }
 qed_status grad_fused(const qed_process* p, const double* uniforms, double sqrt_s, int64_t N, double* out_logm2,
                       double* out_grad, void* stream) {
   long long n = (long long)N;
-  void* args[] = {(void*)&uniforms, (void*)&sqrt_s, (void*)&n, (void*)&out_logm2, (void*)&out_grad};
-  return launch(p->f_grad, N * (int64_t)p->grad_lanes, p->grad_block, stream, args);
+  // Points share their wave's phase-space part, so a wave takes several groups
+  // of points; with few points one each, for the shorter chain
+  int64_t tiles = std::max<int64_t>(1, std::min<int64_t>(64 / p->grad_points, (N + (int64_t)p->grad_points * p->max_waves - 1) / ((int64_t)p->grad_points * p->max_waves)));
+  int t = (int)tiles;
+  const int64_t per = tiles * p->grad_points;
+  void* args[] = {(void*)&uniforms, (void*)&sqrt_s, (void*)&n, (void*)&out_logm2, (void*)&out_grad, (void*)&t};
+  return launch(p->f_grad, (N + per - 1) / per * 64, 64, stream, args);
 }
 qed_status default_process_variant(int n, qed_hel_mode mode, qed_precision prec, int rewrite, qedx::Variant& v) {
   if (!rewrite) return make_variant(n, 1, mode, prec, nullptr, v);

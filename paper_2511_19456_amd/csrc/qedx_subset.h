@@ -29,6 +29,33 @@ template <class T> QEDX_HD void pair_acc(cx<T>& acc, const sp4<T>& X, const sp4<
   acc.r = r;
   acc.i = i;
 }
+// A row adjoint in the column form of its electron line: (-w1, w0, -w3, w2).
+template <class T> QEDX_HD sp4<T> as_column(const sp4<T>& w) {
+  sp4<T> o;
+  o.c[0] = {-w.c[1].r, -w.c[1].i};
+  o.c[1] = w.c[0];
+  o.c[2] = {-w.c[3].r, -w.c[3].i};
+  o.c[3] = w.c[2];
+  return o;
+}
+// Re(w eps-slash C) = e . bil3(w, C) for a real polarisation vector e, and
+// Re(w Q-slash C) = Q0 bil0(w, C) + Q . bil3(w, C), w a row in column form.
+// 24 and 8 FMAs.
+template <class T> QEDX_HD pol3<T> bil3(const sp4<T>& w, const sp4<T>& J) {
+  const cx<T>&a = w.c[0], &b = w.c[1], &c = w.c[2], &d = w.c[3];
+  const cx<T>&L0 = J.c[0], &L1 = J.c[1], &R0 = J.c[2], &R1 = J.c[3];
+  pol3<T> g;
+  g.e1 = a.r * R0.r - a.i * R0.i - b.r * R1.r + b.i * R1.i + d.r * L1.r - d.i * L1.i - c.r * L0.r + c.i * L0.i;
+  g.e2 = d.r * L1.i + d.i * L1.r + c.r * L0.i + c.i * L0.r - b.r * R1.i - b.i * R1.r - a.r * R0.i - a.i * R0.r;
+  g.e3 = d.r * L0.r - d.i * L0.i + c.r * L1.r - c.i * L1.i - b.r * R0.r + b.i * R0.i - a.r * R1.r + a.i * R1.i;
+  return g;
+}
+template <class T> QEDX_HD T bil0(const sp4<T>& w, const sp4<T>& J) {
+  const cx<T>&a = w.c[0], &b = w.c[1], &c = w.c[2], &d = w.c[3];
+  return b.r * J.c[2].r - b.i * J.c[2].i - a.r * J.c[3].r + a.i * J.c[3].i + d.r * J.c[0].r - d.i * J.c[0].i -
+         c.r * J.c[1].r + c.i * J.c[1].i;
+}
+
 #if defined(__HIP_DEVICE_COMPILE__)
 // A current in a wave's LDS region: component k of every lane at p[64 k]
 // (p already offset by the lane), 16 bytes per lane and access.
