@@ -19,12 +19,14 @@ _MODES = {"sum": _lib.HEL_SUM, "per_point": _lib.HEL_PER_POINT}
 _PRECS = {"fp64": _lib.FP64, "fp32c": _lib.FP32C}
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    # the handle of torch.cuda.current_stream() without building the Stream
+    # object, which took 2.9 us of an 8.7 us eval() of a small batch
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _need_gpu() -> None:
