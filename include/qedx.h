@@ -240,16 +240,17 @@ typedef struct {
  * whose body splits a point over 2 or 4 lanes (0 = autotuned: a few
  * grid sizes and tile lengths are timed on the given buffers, which are
  * overwritten, after a device synchronisation; the choice is cached by plan
- * signature).  The plan copies the segment table to the device, allocates a
- * 256-byte tile counter, and instantiates a HIP graph of two kernel nodes
- * (counter clear, persistent kernel).  FP32C plans (per-point processes with
+ * signature).  The plan copies the segment table and the waves' tile ranges
+ * to the device and instantiates a HIP graph of one kernel node, or, for
+ * large FP64 batches of processes without a given kernel shape, one per class
+ * of processes (n = 6; 4, 5; 1..3).  FP32C plans (per-point processes with
  * the FP64 fix-up) also allocate 4(64 + total points) bytes (a counter and a
  * point list per segment) and add two nodes (counter clear, FP64 pass over
  * the listed points, segment by segment); the threshold
  * is the first segment's process's fix_kappa, and the total must stay below
  * 2^31 points.  The segment buffers must stay valid while the plan is
  * launched.  Plans are not thread-safe: launches of one plan on overlapping
- * streams race on its counter. */
+ * streams race on its fix-up counters. */
 qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, int tile_points, qed_batch_plan** out);
 qed_status qed_batch_launch(qed_batch_plan* plan, void* stream);
 qed_status qed_batch_plan_destroy(qed_batch_plan* plan);

@@ -1,13 +1,11 @@
 // qedx_batch.cpp -- mixed-process batches: one persistent kernel over
 // segments of different processes, replayed from a captured HIP graph.
 //
-// Work is cut into tiles of 64 * chunk points of one segment; each wavefront
-// takes tiles from a device counter (one vector atomic per tile) until none
-// are left, evaluating its tile with the body of that segment's process.
-// Segments are laid out in the tile space by decreasing cost per point (the
-// static FLOP count of their graphs), so the long tiles are taken first and
-// the short ones fill the tail.  The counter is cleared by a one-thread kernel
-// node in the same graph (no memset node).  Grid size and tile length are
+// Work is cut into tiles of 64 * chunk lanes of one segment, laid out by
+// decreasing cost per point (the static FLOP count of the kernels).  Each
+// wavefront takes its share of the tile space -- every W-th tile of W waves, or
+// (pair kernels) a contiguous range, cut on the host to equal cost -- and
+// evaluates it with the bodies of its segments' processes.  Grid size and tile length are
 // picked by timing a few candidates once per plan signature; the choice is
 // kept in autotune.txt in the code-object cache directory.
 #include <hip/hip_runtime_api.h>
@@ -114,8 +112,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   os << "struct qedx_seg { const double* mom; const unsigned* hel; double* out; long long N; long long tile0; "
         "int proc; int shift; int shift64; long long list0; };\n";
   os << "extern \"C\" __global__ void __launch_bounds__(256)\n"
-        "qedx_batch(const qedx_seg* __restrict__ segs, int nseg, long long ntiles, int chunk, "
-        "unsigned* __restrict__ counter"
+        "qedx_batch(const qedx_seg* __restrict__ segs, int nseg, long long ntiles, int chunk"
      << (fix ? ", double fix_kappa, unsigned* __restrict__ fix_cnt, unsigned* __restrict__ fix_list" : "")
      << ")\n{\n";
   std::string PT = "double";
@@ -124,19 +121,15 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   if (pol_npart > 0) os << "  __shared__ " << PT << " qx_pol_mem[" << 3 * pol_npart * 256 << "];\n";
   if (cache_w > 0) os << "  __shared__ double2 qx_cache_mem[" << 2 * cache_w << "];\n";
   os << "  const int lane = threadIdx.x & 63;\n";
-  os << "  while (true) {\n";
-  os << "    unsigned t = 0;\n";
-  os << "    if (lane == 0) t = atomicAdd(counter, 1u);\n";
-  os << "    t = __shfl(t, 0);\n";
-  os << "    if ((long long)t >= ntiles) break;\n";
-  os << "    int s = 0;\n";
-  os << "    while (s + 1 < nseg && segs[s + 1].tile0 <= (long long)t) ++s;\n";
+  os << "  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (threadIdx.x >> 6)));\n";
+  os << "  int s = 0;\n  for (long long t = w; t < ntiles; t += 4ll * gridDim.x) {\n";
+  os << "    while (s + 1 < nseg && segs[s + 1].tile0 <= t) ++s;\n";
   os << "    const qedx_seg sg = segs[s];\n";
   os << "    const int lp = lane >> sg.shift;\n";
   os << "    const unsigned sub = (unsigned)(lane & ((1 << sg.shift) - 1));\n";
   os << "    const long long ppw = 64LL >> sg.shift;\n";
   os << "    for (int c = 0; c < chunk; ++c) {\n";
-  os << "      const long long pt = ((long long)t - sg.tile0) * ppw * chunk + ppw * c + lp;\n";
+  os << "      const long long pt = (t - sg.tile0) * ppw * chunk + ppw * c + lp;\n";
   os << "      if (pt - lp >= sg.N) break;\n";
   os << "      const long long ptc = pt < sg.N ? pt : sg.N - 1;\n";
   os << "      const unsigned hrt = sg.hel[ptc];\n";
@@ -169,9 +162,10 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
        << "        }\n      }\n";
   }
   os << "    }\n  }\n}\n";
-  // clears the 64 counters at c (the tile counter, or one per segment)
-  os << "extern \"C\" __global__ void qedx_zero(unsigned* __restrict__ c)\n{\n"
-        "  if (blockIdx.x == 0 && threadIdx.x < 64) c[threadIdx.x] = 0u;\n}\n";
+  // clears the 64 counters at c (fix-up points of the segments)
+  if (fix)
+    os << "extern \"C\" __global__ void qedx_zero(unsigned* __restrict__ c)\n{\n"
+          "  if (blockIdx.x == 0 && threadIdx.x < 64) c[threadIdx.x] = 0u;\n}\n";
   if (fix) {
     // every wave walks the segments in turn and takes its share of each
     // segment's list, 64 >> shift points per round (all lanes take part in
@@ -207,7 +201,93 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   return os.str();
 }
 
+// ---------------------------------------------------------------------------
+// Plans whose processes all take the pair kernels (FP64, no kernel shape asked
+// for) share one module for n = 1..6, so no plan waits for a compiler.  It
+// holds a kernel for all processes, for batches too small to fill the device,
+// and one per class of processes with registers and LDS of that class: in the
+// common kernel the 7-photon body leaves every other one a single wave per
+// SIMD and none of the LDS.  A wave's tiles are a contiguous range of the tile
+// space, cut on the host by the segments' cost: taking them from a counter
+// cost 5.8 ns per tile in the counter's memory alone (86,000 tiles of the
+// n = 1..6 batch: 1.43 ms, and 0.94 ms with four rounds of points per tile),
+// and a range's next inputs can be loaded ahead.
+// ---------------------------------------------------------------------------
+struct PairClass {
+  const char* name;
+  int lo, hi;  // outgoing photons
+  int waves;   // waves per SIMD
+};
+const PairClass kPairClasses[] = {{"qedx_batch_n6", 6, 6, 1}, {"qedx_batch_n45", 4, 5, 1}, {"qedx_batch_n13", 1, 3, 2}};
+const int kClasses = 3;
+int pair_class(int n) { return n == 6 ? 0 : n >= 4 ? 1 : 2; }
+
+std::string pair_module_source() {
+  std::ostringstream os;
+  os << "// generated by qedx: mixed-process batch module\n#include <hip/hip_runtime.h>\n";
+  os << device_header_text() << "\n" << subset_header_text() << "\n";
+  os << "struct qedx_seg { const double* mom; const unsigned* hel; double* out; long long N; long long tile0; "
+        "int proc; int shift; int shift64; long long list0; };\n";
+  for (int n = 1; n <= 6; ++n) {
+    const Process pr = Process::make(n, 1);
+    const std::string b = "qedx_body_" + std::to_string(n);
+    EmitStats st;
+    os << emit_pair_body(pr, b, &st) << "\n";
+    // `rounds` times 32 points; up to 6 photons the next round's inputs are
+    // loaded while this one's are worked on
+    os << "static __device__ __forceinline__ void qedx_run_" << n
+       << "(const qedx_seg& sg, long long p0, long long rounds, double* __restrict__ lds)\n{\n";
+    os << "  long long pt = p0 + (__lane_id() >> 1);\n";
+    os << "  " << b << "_in cur;\n  " << b << "_load(sg.mom, sg.hel, sg.N, pt < sg.N ? pt : sg.N - 1, cur);\n";
+    os << "  while (true) {\n    const bool more = --rounds > 0;\n    const long long nx = pt + 32;\n";
+    if (n < 6) {
+      os << "    " << b << "_in nin = cur;\n    if (more) " << b << "_load(sg.mom, sg.hel, sg.N, nx < sg.N ? nx : sg.N - 1, nin);\n";
+      os << "    __builtin_amdgcn_sched_barrier(0);\n";
+    }
+    os << "    const double r = " << b << "_run(cur, lds);\n";
+    os << "    if (pt < sg.N && (__lane_id() & 1u) == 0u) sg.out[pt] = r;\n";
+    os << "    if (!more) break;\n    pt = nx;\n";
+    if (n < 6)
+      os << "    cur = nin;\n";
+    else
+      os << "    " << b << "_load(sg.mom, sg.hel, sg.N, pt < sg.N ? pt : sg.N - 1, cur);\n";
+    os << "  }\n}\n";
+  }
+  auto kernel = [&](const std::string& name, int lo, int hi, int waves) {
+    int W = 0;
+    for (int n = lo; n <= hi; ++n) W = std::max(W, pair_lds_doubles(Process::make(n, 1)));
+    os << "extern \"C\" __global__ void __launch_bounds__(256, " << waves << ")\n" << name
+       << "(const qedx_seg* __restrict__ segs, int nseg, const long long* __restrict__ cut, int chunk)\n{\n";
+    if (W) os << "  __shared__ double2 qx_lds[" << 2 * W << "];\n";
+    os << "  double* const lds = " << (W ? "(double*)qx_lds + (threadIdx.x >> 6) * " + std::to_string(W) : std::string("nullptr"))
+       << ";\n";
+    os << "  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (threadIdx.x >> 6)));\n";
+    os << "  long long t = cut[w];\n  const long long end = cut[w + 1];\n  int s = 0;\n  while (t < end) {\n";
+    os << "    while (s + 1 < nseg && segs[s + 1].tile0 <= t) ++s;\n";
+    os << "    const qedx_seg sg = segs[s];\n";
+    os << "    const long long stop = s + 1 < nseg && segs[s + 1].tile0 < end ? segs[s + 1].tile0 : end;\n";
+    os << "    const long long p0 = (t - sg.tile0) * 32 * chunk, left = (sg.N - p0 + 31) >> 5, all = (stop - t) * chunk;\n";
+    os << "    const long long rounds = all < left ? all : left;\n    t = stop;\n    switch (sg.proc) {\n";
+    for (int n = lo; n <= hi; ++n) os << "      case " << n << ": qedx_run_" << n << "(sg, p0, rounds, lds); break;\n";
+    os << "      default: break;\n    }\n  }\n}\n";
+  };
+  kernel("qedx_batch", 1, 6, 1);
+  for (const PairClass& c : kPairClasses) kernel(c.name, c.lo, c.hi, c.waves);
+  return os.str();
+}
+
+// Relative time of a point: its FLOPs, and 1500 more for what the smallest
+// processes wait for.
+double tile_cost(double flops_per_point) { return flops_per_point + 1500.0; }
+
+bool all_pair(const std::vector<std::pair<Process, Variant>>& pv) {
+  for (auto& p : pv)
+    if (p.second.prec != PREC_F64 || p.first.n_in != 1 || !pair_kernel(p.first, p.second)) return false;
+  return true;
+}
+
 std::string batch_tag(const std::vector<std::pair<Process, Variant>>& pv) {
+  if (all_pair(pv)) return "batch_pair_f64";
   std::string tag = "batch";
   for (auto& p : pv) tag += "_n" + std::to_string(p.first.n_out) + (p.second.rewrite ? "d" + std::to_string(p.second.rewrite) : "");
   tag += pv.empty() || pv[0].second.prec == PREC_F64 ? "_f64" : "_f32c";
@@ -242,10 +322,16 @@ void tune_store(const std::string& key, int grid, int chunk) {
 }  // namespace
 
 struct qed_batch_plan {
+  bool pair = false;      // the module of the pair kernels
+  bool classes = false;   // ... one kernel per class of processes
+  hipFunction_t f_class[kClasses] = {};
+  long long cls_tile[kClasses + 1] = {};  // tiles of a class
+  long long* d_cut = nullptr;             // first tile of every wave, and the end, of each kernel in turn
+  int cut_at[kClasses] = {}, cut_groups[kClasses] = {};  // ... where a kernel's start, its workgroups
+  int ncu = 256;
   hipModule_t mod = nullptr;
   hipFunction_t f_batch = nullptr, f_zero = nullptr, f_fix = nullptr;
   DevSeg* d_segs = nullptr;
-  unsigned* d_counter = nullptr;
   unsigned* d_fix = nullptr;  // FP32C fix-up: [64 per-segment counts, point lists of the segments]
   double fix_kappa = 0;
   long long fix_grid = 0;
@@ -266,19 +352,29 @@ struct qed_batch_plan {
       (void)hipStreamDestroy(cap);
     }
     if (d_segs) (void)hipFree(d_segs);
-    if (d_counter) (void)hipFree(d_counter);
+    if (d_cut) (void)hipFree(d_cut);
     if (d_fix) (void)hipFree(d_fix);
     if (mod) (void)hipModuleUnload(mod);
   }
 };
 
 static qed_status launch_eager(qed_batch_plan* b, hipStream_t s) {
-  void* za[] = {(void*)&b->d_counter};
-  hipError_t e = hipModuleLaunchKernel(b->f_zero, 1, 1, 1, 64, 1, 1, 0, s, za, nullptr);
-  if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("zero kernel: ") + hipGetErrorString(e));
+  hipError_t e;
+  if (b->pair) {
+    for (int c = 0; c < (b->classes ? kClasses : 1); ++c) {
+      if (!b->cut_groups[c]) continue;
+      const long long* cut = b->d_cut + b->cut_at[c];
+      void* ba[] = {(void*)&b->d_segs, (void*)&b->nseg, (void*)&cut, (void*)&b->chunk};
+      e = hipModuleLaunchKernel(b->classes ? b->f_class[c] : b->f_batch, (unsigned)b->cut_groups[c], 1, 1, 256, 1, 1, 0, s, ba,
+                                nullptr);
+      if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("batch kernel: ") + hipGetErrorString(e));
+    }
+    return QED_OK;
+  }
+  const unsigned groups = (unsigned)b->grid;
   if (!b->f_fix) {
-    void* ba[] = {(void*)&b->d_segs, (void*)&b->nseg, (void*)&b->ntiles, (void*)&b->chunk, (void*)&b->d_counter};
-    e = hipModuleLaunchKernel(b->f_batch, (unsigned)b->grid, 1, 1, 256, 1, 1, 0, s, ba, nullptr);
+    void* ba[] = {(void*)&b->d_segs, (void*)&b->nseg, (void*)&b->ntiles, (void*)&b->chunk};
+    e = hipModuleLaunchKernel(b->f_batch, groups, 1, 1, 256, 1, 1, 0, s, ba, nullptr);
     if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("batch kernel: ") + hipGetErrorString(e));
     return QED_OK;
   }
@@ -287,9 +383,9 @@ static qed_status launch_eager(qed_batch_plan* b, hipStream_t s) {
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("zero kernel: ") + hipGetErrorString(e));
   unsigned* cnt = b->d_fix;
   unsigned* list = b->d_fix + 64;
-  void* ba[] = {(void*)&b->d_segs, (void*)&b->nseg,      (void*)&b->ntiles, (void*)&b->chunk,
-                (void*)&b->d_counter, (void*)&b->fix_kappa, (void*)&cnt,       (void*)&list};
-  e = hipModuleLaunchKernel(b->f_batch, (unsigned)b->grid, 1, 1, 256, 1, 1, 0, s, ba, nullptr);
+  void* ba[] = {(void*)&b->d_segs,    (void*)&b->nseg, (void*)&b->ntiles, (void*)&b->chunk,
+                (void*)&b->fix_kappa, (void*)&cnt,     (void*)&list};
+  e = hipModuleLaunchKernel(b->f_batch, groups, 1, 1, 256, 1, 1, 0, s, ba, nullptr);
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("batch kernel: ") + hipGetErrorString(e));
   void* fa[] = {(void*)&b->d_segs, (void*)&b->nseg, (void*)&cnt, (void*)&list};
   e = hipModuleLaunchKernel(b->f_fix, (unsigned)b->fix_grid, 1, 1, 256, 1, 1, 0, s, fa, nullptr);
@@ -303,16 +399,27 @@ static qed_status layout_tiles(qed_batch_plan* b, const qed_segment* segs, const
   std::vector<int> ord(b->nseg);
   for (int i = 0; i < b->nseg; ++i) ord[i] = i;
   std::stable_sort(ord.begin(), ord.end(), [&](int a, int c) { return cost[a] > cost[c]; });
+  // (the pair module's classes come in that order)
+  if (b->pair)
+    std::stable_sort(ord.begin(), ord.end(),
+                     [&](int a, int c) { return pair_class(segs[a].proc->n) < pair_class(segs[c].proc->n); });
   b->host.clear();
   long long t0 = 0, l0 = 0;
+  int cls = 0;
+  b->cls_tile[0] = 0;
+  auto close_to = [&](int c) {
+    for (; cls < c; ++cls) b->cls_tile[cls + 1] = t0;
+  };
+  std::vector<std::pair<long long, double>> tiles;  // end and cost per tile of every segment, in tile order
   for (int i : ord) {
+    if (b->pair) close_to(pair_class(segs[i].proc->n));
     DevSeg d;
     d.mom = segs[i].momenta;
     d.hel = segs[i].hel;
     d.out = segs[i].out;
     d.N = segs[i].N;
     d.tile0 = t0;
-    d.proc = proc_of[i];
+    d.proc = b->pair ? segs[i].proc->n : proc_of[i];
     d.shift = b->shift[proc_of[i]];
     d.shift64 = b->shift64[proc_of[i]];
     d.list0 = l0;
@@ -320,8 +427,48 @@ static qed_status layout_tiles(qed_batch_plan* b, const qed_segment* segs, const
     b->host.push_back(d);
     const long long per = (64LL >> d.shift) * b->chunk;  // points per tile
     t0 += (segs[i].N + per - 1) / per;
+    tiles.push_back({t0, tile_cost(cost[i])});
   }
+  close_to(kClasses);
   b->ntiles = t0;
+  if (b->pair) {
+    std::vector<long long> cut;
+    for (int c = 0; c < (b->classes ? kClasses : 1); ++c) {
+      const long long lo = b->classes ? b->cls_tile[c] : 0, hi = b->classes ? b->cls_tile[c + 1] : t0;
+      const long long most = b->classes ? (long long)b->ncu * kPairClasses[c].waves : b->ncu;
+      const long long groups = std::min<long long>((hi - lo + 3) / 4, most);
+      const long long W = 4 * groups;
+      b->cut_at[c] = (int)cut.size();
+      b->cut_groups[c] = (int)groups;
+      if (!groups) continue;
+      // wave w starts at the first tile with at least w / W of the cost before it
+      double total = 0;
+      long long t = lo;
+      for (auto& g : tiles)
+        if (g.first > t) {
+          total += (double)(std::min(g.first, hi) - t) * g.second;
+          t = std::max(t, std::min(g.first, hi));
+        }
+      double before = 0;
+      t = lo;
+      size_t g = 0;
+      for (long long w = 0; w < W; ++w) {
+        const double want = total * (double)w / (double)W;
+        while (t < hi) {
+          while (tiles[g].first <= t) ++g;
+          if (before >= want - 1e-9 * total) break;
+          const long long room = std::min(tiles[g].first, hi) - t;
+          const long long n = std::min<long long>(room, std::max<long long>(1, (long long)((want - before) / tiles[g].second)));
+          before += (double)n * tiles[g].second;
+          t += n;
+        }
+        cut.push_back(t);
+      }
+      cut.push_back(hi);
+    }
+    hipError_t e = hipMemcpy(b->d_cut, cut.data(), sizeof(long long) * cut.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("tile ranges copy: ") + hipGetErrorString(e));
+  }
   hipError_t e = hipMemcpy(b->d_segs, b->host.data(), sizeof(DevSeg) * b->host.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("segment table copy: ") + hipGetErrorString(e));
   return QED_OK;
@@ -375,8 +522,9 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   std::string src;
   std::vector<std::pair<Process, Variant>> pv;
   for (auto* p : procs) pv.push_back({p->proc, batch_variant(p->var)});
+  b->pair = all_pair(pv);
   try {
-    src = module_source(pv);
+    src = b->pair ? pair_module_source() : module_source(pv);
   } catch (const std::exception& e) {
     return fail(QED_ERR_INVALID_ARG, std::string("batch emit: ") + e.what());
   }
@@ -393,14 +541,15 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   };
   if ((st = chk(hipModuleLoadData(&b->mod, co.data()), "load batch module"))) return st;
   if ((st = chk(hipModuleGetFunction(&b->f_batch, b->mod, "qedx_batch"), "qedx_batch"))) return st;
-  if ((st = chk(hipModuleGetFunction(&b->f_zero, b->mod, "qedx_zero"), "qedx_zero"))) return st;
-  if (hipMalloc((void**)&b->d_segs, sizeof(DevSeg) * nseg) != hipSuccess ||
-      hipMalloc((void**)&b->d_counter, 256) != hipSuccess)
+  for (int c = 0; b->pair && c < kClasses; ++c)
+    if ((st = chk(hipModuleGetFunction(&b->f_class[c], b->mod, kPairClasses[c].name), kPairClasses[c].name))) return st;
+  if (hipMalloc((void**)&b->d_segs, sizeof(DevSeg) * nseg) != hipSuccess)
     return fail(QED_ERR_OOM, "segment table allocation failed");
   if (module_fixup(pv)) {
     long long total = 0;
     for (int i = 0; i < nseg; ++i) total += segs[i].N;
     if (total >= (1LL << 31)) return fail(QED_ERR_INVALID_ARG, "FP32C batches with the FP64 fix-up take < 2^31 points");
+    if ((st = chk(hipModuleGetFunction(&b->f_zero, b->mod, "qedx_zero"), "qedx_zero"))) return st;
     if ((st = chk(hipModuleGetFunction(&b->f_fix, b->mod, "qedx_batch_fix"), "qedx_batch_fix"))) return st;
     if (hipMalloc((void**)&b->d_fix, sizeof(unsigned) * (64 + (size_t)std::max<long long>(total, 1))) != hipSuccess)
       return fail(QED_ERR_OOM, "fix-up list allocation failed");
@@ -412,7 +561,13 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
 
+  b->ncu = ncu;
+  // four waves per workgroup, up to four workgroups per compute unit
+  if (b->pair && hipMalloc((void**)&b->d_cut, sizeof(long long) * ((size_t)16 * ncu + kClasses)) != hipSuccess)
+    return fail(QED_ERR_OOM, "tile range allocation failed");
   // plan signature for the autotune cache
+  long long total_lanes = 0;
+  for (int i = 0; i < nseg; ++i) total_lanes += segs[i].N << b->shift[proc_of[i]];
   std::ostringstream key;
   key << tag;
   for (int i = 0; i < nseg; ++i) key << "_" << segs[i].proc->n << "x" << segs[i].N;
@@ -420,18 +575,30 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   if (tile_points > 0) {
     chunk = tile_points / 64;
     grid = ncu * 2;
+    // one kernel per class where the batch fills the device several times over
+    b->classes = b->pair && total_lanes >= (long long)ncu * 256 * 8;
   } else if (!tune_lookup(key.str(), grid, chunk)) {
     // time candidates: workgroups per CU (x 4 waves) and tile length.  The
     // inputs may still be in flight on another stream: wait for the device.
     if ((st = chk(hipDeviceSynchronize(), "autotune sync"))) return st;
-    double best = 1e30;
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);
     (void)hipEventCreate(&e1);
-    for (int wpc : {1, 2, 4}) {
-      for (int ch : {1, 4, 16}) {
-        b->grid = ncu * wpc;
-        b->chunk = ch;
+    // twice over all candidates, the better time of each: the first launches
+    // after a pause run at a lower clock
+    struct Candidate {
+      int wpc, chunk;
+      float ms;
+    };
+    std::vector<Candidate> cand;
+    for (int wpc : {0, 1, 2, 4})  // 0: a kernel per class
+      for (int ch : {1, 4, 16})
+        if (b->pair ? wpc <= 1 && ch <= 4 : wpc > 0) cand.push_back({wpc, ch, 1e30f});
+    for (int pass = 0; pass < 2; ++pass)
+      for (Candidate& c : cand) {
+        b->classes = c.wpc == 0;
+        b->grid = ncu * c.wpc;
+        b->chunk = c.chunk;
         if ((st = layout_tiles(b.get(), segs, proc_of, cost))) return st;
         if ((st = launch_eager(b.get(), b->cap))) return st;  // warm
         (void)hipEventRecord(e0, b->cap);
@@ -441,17 +608,16 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
         if ((st = chk(hipEventSynchronize(e1), "autotune sync"))) return st;
         float t = 0;
         (void)hipEventElapsedTime(&t, e0, e1);
-        if (t < best) {
-          best = t;
-          grid = b->grid;
-          chunk = ch;
-        }
+        c.ms = std::min(c.ms, t);
       }
-    }
+    const Candidate& best = *std::min_element(cand.begin(), cand.end(), [](const Candidate& x, const Candidate& y) { return x.ms < y.ms; });
+    grid = ncu * best.wpc;
+    chunk = best.chunk;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     tune_store(key.str(), grid, chunk);
   }
+  if (!tile_points) b->classes = b->pair && grid == 0;
   b->grid = grid;
   b->chunk = chunk;
   if ((st = layout_tiles(b.get(), segs, proc_of, cost))) return st;
@@ -484,7 +650,7 @@ extern "C" qed_status qed_batch_plan_destroy(qed_batch_plan* plan) {
 extern "C" qed_status qed_batch_info(const qed_batch_plan* plan, int64_t* ntiles, int* grid, int* chunk) {
   if (!plan) return fail(QED_ERR_INVALID_ARG, "plan is NULL");
   if (ntiles) *ntiles = plan->ntiles;
-  if (grid) *grid = plan->grid;
+  if (grid) *grid = plan->classes ? plan->ncu : plan->grid;
   if (chunk) *chunk = plan->chunk;
   return QED_OK;
 }
@@ -506,7 +672,7 @@ extern "C" qed_status qed_batch_prebuild(const int* n_list, int count, qed_preci
   }
   std::string src;
   try {
-    src = module_source(pv);
+    src = all_pair(pv) ? pair_module_source() : module_source(pv);
   } catch (const std::exception& e) {
     return fail(QED_ERR_INVALID_ARG, std::string("batch emit: ") + e.what());
   }

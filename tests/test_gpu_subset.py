@@ -116,3 +116,37 @@ def test_gradient_tile_edges(n, sqrt_s):
     assert np.abs(val[idx].cpu().numpy() - v_o.numpy()).max() < 1e-10 * max(1.0, np.abs(v_o.numpy()).max())
     err = np.linalg.norm(g[:, idx].cpu().numpy() - g_o.numpy(), axis=0) / np.linalg.norm(g_o.numpy(), axis=0)
     assert err.max() < 1e-10
+
+
+@pytest.mark.parametrize("tile", [64, 256, 4096, 0])
+@pytest.mark.parametrize("big", [False, True])
+def test_batch_tile_ranges(tile, big):
+    """Mixed batches cut into per-wave tile ranges, below and above the size
+    from which each class of processes has its own kernel: empty, single-point
+    and ragged segments, several of one process, classes without a segment.
+    Every point against the per-process kernel (same code per point, so the
+    rounding of one reordered sum at most) and none written past its end."""
+    from paper_2511_19456_amd.qedx import BatchPlan, QedProcess
+    spec = [(3, 65), (6, 33), (1, 1), (5, 0), (2, 4097), (6, 1), (4, 130), (3, 31), (1, 777)]
+    if big:
+        ncu = torch.cuda.get_device_properties(0).multi_processor_count
+        spec += [(2, 900 * ncu + 5), (1, 200 * ncu + 31), (6, 4 * ncu + 3)]   # no 4 or 5 photon bulk
+    procs, segs, ends, refs = {}, [], [], []
+    for k, (n, N) in enumerate(spec):
+        p = procs.setdefault(n, QedProcess(n, "per_point"))
+        u, hel = inputs.rambo_inputs(400 + k, n, N, with_helicities=True)
+        mom = p.rambo(torch.as_tensor(u, device=DEV), 6.0 + 3 * n)
+        h = torch.as_tensor(hel.astype(np.int32), device=DEV)
+        buf = torch.full((N + 1,), -7.0, dtype=torch.float64, device=DEV)
+        ends.append(buf)
+        segs.append((p, mom, h, buf[:N]))
+        refs.append(p.eval(mom, h) if N else buf[:0].clone())
+    plan = BatchPlan(segs, tile_points=tile)
+    for rep in range(2):
+        for b in ends:
+            b.fill_(-7.0)
+        plan.launch()
+        torch.cuda.synchronize()
+        for (n, N), b, r in zip(spec, ends, refs):
+            assert b[N].item() == -7.0, (n, N)
+            assert N == 0 or ((b[:N] - r).abs() <= 1e-13 * r.abs()).all(), (n, N, rep)
