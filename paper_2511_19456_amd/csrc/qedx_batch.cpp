@@ -224,7 +224,7 @@ int pair_class(int n) { return n == 6 ? 0 : n >= 4 ? 1 : 2; }
 
 std::string pair_module_source() {
   std::ostringstream os;
-  os << "// generated by qedx: mixed-process batch module\n#include <hip/hip_runtime.h>\n";
+  os << "// generated by qedx: mixed-process batch module\n" << kContractOn << "#include <hip/hip_runtime.h>\n";
   os << device_header_text() << "\n" << subset_header_text() << "\n";
   os << "struct qedx_seg { const double* mom; const unsigned* hel; double* out; long long N; long long tile0; "
         "int proc; int shift; int shift64; long long list0; };\n";

@@ -241,7 +241,7 @@ std::string emit_pair_body(const Process& pr, const std::string& fname, EmitStat
 std::string emit_pair_kernel(const Process& pr, const Variant& v, const std::string& kname, EmitStats* st) {
   std::ostringstream os;
   os << "// generated by qedx: " << variant_tag(v, pr.n_out, pr.n_in) << "\n";
-  os << "// subset currents, lane 0 of a point from e-_in, lane 1 from e-_out\n";
+  os << kContractOn << "// subset currents, lane 0 of a point from e-_in, lane 1 from e-_out\n";
   os << "#include <hip/hip_runtime.h>\n" << device_header_text() << "\n" << subset_header_text() << "\n";
   const std::string body = kname + "_body";
   os << emit_pair_body(pr, body, st);

@@ -35,6 +35,10 @@
 
 namespace qedx {
 
+// Second line of the sources compiled with FMAs formed within an expression
+// only: a process's eval kernel and the batch kernels give the same bits.
+constexpr const char* kContractOn = "// fp-contract: on\n";
+
 // Whether (process, variant) is evaluated by the pair kernels.
 inline bool pair_kernel(const Process& pr, const Variant& v) { return v.subset && v.mode == HEL_PER_POINT; }
 

@@ -97,12 +97,16 @@ static std::string hex64(uint64_t v) {
 
 static const char* kArch = "gfx950";
 
-static std::vector<std::string> compile_flags() {
+// Sources with kContractOn as their second line form FMAs within an expression only, so
+// the same code rounds alike in every kernel it is inlined into.
+static std::vector<std::string> compile_flags(const std::string& src) {
+  const size_t nl = src.find('\n');
+  const bool on = nl != std::string::npos && src.compare(nl + 1, strlen(kContractOn), kContractOn) == 0;
   std::vector<std::string> f = {"--offload-arch=gfx950",
                                 "-O3",
                                 "--genco",
                                 "-std=c++17",
-                                "-ffp-contract=fast",
+                                on ? "-ffp-contract=on" : "-ffp-contract=fast",
                                 "-Xclang",
                                 "-target-feature",
                                 "-Xclang",
@@ -144,9 +148,10 @@ static bool write_file(const std::string& path, const std::string& data) {
 }
 
 // Run hipcc as a child process (never replaces this process).
-static int run_hipcc(const std::string& src, const std::string& out, const std::string& log, double timeout_s) {
+static int run_hipcc(const std::string& src, const std::string& text, const std::string& out, const std::string& log,
+                     double timeout_s) {
   std::vector<std::string> args = {hipcc_path()};
-  for (auto& f : compile_flags()) args.push_back(f);
+  for (auto& f : compile_flags(text)) args.push_back(f);
   args.push_back(src);
   args.push_back("-o");
   args.push_back(out);
@@ -201,7 +206,7 @@ static std::mutex g_cache_mu;
 static qed_status get_code_object(const std::string& tag, const std::string& src, std::string& co,
                                   KernelMeta& meta, bool& hit, double& ms) {
   std::string key_material = src;
-  for (auto& f : compile_flags()) key_material += "\n" + f;
+  for (auto& f : compile_flags(src)) key_material += "\n" + f;
   key_material += std::string("\n") + kArch;
   std::string h = hex64(fnv1a(key_material.data(), key_material.size()));
   std::string base = cache_dir_str() + "/" + tag + "-" + h;
@@ -231,7 +236,7 @@ static qed_status get_code_object(const std::string& tag, const std::string& src
   double tmo = 3600.0;
   if (const char* t = getenv("QEDX_COMPILE_TIMEOUT")) tmo = atof(t);
   auto t0 = std::chrono::steady_clock::now();
-  int rc = run_hipcc(srcp, tmpo, tmpl, tmo);
+  int rc = run_hipcc(srcp, src, tmpo, tmpl, tmo);
   ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   std::string lg;
   read_file(tmpl, lg);
