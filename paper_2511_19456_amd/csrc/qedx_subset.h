@@ -38,9 +38,8 @@ template <class T> QEDX_HD sp4<T> as_column(const sp4<T>& w) {
   o.c[3] = w.c[2];
   return o;
 }
-// Re(w eps-slash C) = e . bil3(w, C) for a real polarisation vector e, and
 // Re(w Q-slash C) = Q0 bil0(w, C) + Q . bil3(w, C), w a row in column form.
-// 24 and 8 FMAs.
+// 8 and 24 FMAs.
 template <class T> QEDX_HD pol3<T> bil3(const sp4<T>& w, const sp4<T>& J) {
   const cx<T>&a = w.c[0], &b = w.c[1], &c = w.c[2], &d = w.c[3];
   const cx<T>&L0 = J.c[0], &L1 = J.c[1], &R0 = J.c[2], &R1 = J.c[3];
