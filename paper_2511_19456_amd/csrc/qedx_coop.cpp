@@ -51,8 +51,9 @@ struct Coop {
     // Lanes 0-3, 12-15 and 20-27 of a wave read 16 bytes each in one pass over
     // the 64 banks: the points' offsets keep their slots apart (12 of 16 for 8
     // lanes per point: 433 us instead of 444 with 8, 490 with 1 or 0, 2^20
-    // points of 4 photons)
-    while (PPW > 1 && PT % 16 != (L == 8 ? 12 : L % 16)) ++PT;
+    // points of 4 photons; 8 for 16 lanes: 1344 instead of 1360 us with 0, the
+    // gradient of 2^18 points of 5 photons, 40 % of the conflicts)
+    while (PPW > 1 && PT % 16 != (L == 8 ? 12 : L == 16 ? 8 : L % 16)) ++PT;
   }
   int items(int k) const { return (int)lv[k].size() << k; }
   int rounds(int k) const { return (items(k) + L - 1) / L; }
