@@ -16,6 +16,18 @@ template <class T> QEDX_HD void vL_add(sp4<T>& o, const sp4<T>& J, const pol3<T>
   o.c[3].r = o.c[3].r + e.e1 * L0.r - e.e2 * L0.i - e.e3 * L1.r;
   o.c[3].i = o.c[3].i + e.e1 * L0.i + e.e2 * L0.r - e.e3 * L1.i;
 }
+// The same for the polarisation across the z axis, e3 = 0: 8 x 2 FMAs
+template <class T> QEDX_HD void vL_add_flat(sp4<T>& o, const sp4<T>& J, T e1, T e2) {
+  const cx<T>&L0 = J.c[0], &L1 = J.c[1], &R0 = J.c[2], &R1 = J.c[3];
+  o.c[0].r = o.c[0].r - e1 * R1.r - e2 * R1.i;
+  o.c[0].i = o.c[0].i - e1 * R1.i + e2 * R1.r;
+  o.c[1].r = o.c[1].r - e1 * R0.r + e2 * R0.i;
+  o.c[1].i = o.c[1].i - e1 * R0.i - e2 * R0.r;
+  o.c[2].r = o.c[2].r + e1 * L1.r + e2 * L1.i;
+  o.c[2].i = o.c[2].i + e1 * L1.i - e2 * L1.r;
+  o.c[3].r = o.c[3].r + e1 * L0.r - e2 * L0.i;
+  o.c[3].i = o.c[3].i + e1 * L0.i + e2 * L0.r;
+}
 // The join with the row current written as the column (-B1, B0, -B3, B2):
 // acc += X1 Y0 - X0 Y1 + X3 Y2 - X2 Y3 (antisymmetric in X, Y).        32 FLOPs
 template <class T> QEDX_HD void pair_acc(cx<T>& acc, const sp4<T>& X, const sp4<T>& Y) {
