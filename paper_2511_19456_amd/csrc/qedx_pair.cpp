@@ -211,6 +211,11 @@ int pair_lds_doubles(const Process& pr) { return pr.P >= 7 ? 512 * kSlots + 32 *
 
 int pair_waves(const Process& pr) { return pr.P >= 5 ? 1 : 2; }
 
+// 7 photons: a workgroup of four waves would hold the whole LDS until its last
+// wave ends; single waves make way as they end (64 points 30.1 -> 28.0 us, 10^6
+// points 968 -> 914 us).
+int pair_block(const Process& pr) { return pair_lds_doubles(pr) > 0 ? 64 : 256; }
+
 bool pair_persistent(const Process& pr) { return pr.P == 5 || pr.P == 6; }
 
 std::string emit_pair_body(const Process& pr, const std::string& fname, EmitStats* st) {
@@ -245,12 +250,12 @@ std::string emit_pair_kernel(const Process& pr, const Variant& v, const std::str
   os << "#include <hip/hip_runtime.h>\n" << device_header_text() << "\n" << subset_header_text() << "\n";
   const std::string body = kname + "_body";
   os << emit_pair_body(pr, body, st);
-  const int W = pair_lds_doubles(pr);
-  os << "extern \"C\" __global__ void __launch_bounds__(256, " << pair_waves(pr) << ")\n" << kname
+  const int W = pair_lds_doubles(pr), B = pair_block(pr);
+  os << "extern \"C\" __global__ void __launch_bounds__(" << B << ", " << pair_waves(pr) << ")\n" << kname
      << "(const double* __restrict__ mom, const unsigned* __restrict__ hel, long long N, double* __restrict__ out)\n{\n";
-  if (W) os << "  __shared__ double2 qx_lds[" << 4 * W / 2 << "];\n";
+  if (W) os << "  __shared__ double2 qx_lds[" << B / 64 * W / 2 << "];\n";
   const std::string lds = W ? "(double*)qx_lds + (threadIdx.x >> 6) * " + std::to_string(W) : std::string("nullptr");
-  os << "  long long pt = ((long long)blockIdx.x * 256 + threadIdx.x) >> 1;\n";
+  os << "  long long pt = ((long long)blockIdx.x * " << B << " + threadIdx.x) >> 1;\n";
   if (pair_persistent(pr)) {
     // one wave per SIMD: the next points' inputs are loaded while this one's are worked on
     os << "  const long long step = 128LL * gridDim.x;\n";

@@ -50,6 +50,8 @@ std::string emit_pair_body(const Process& pr, const std::string& fname, EmitStat
 int pair_lds_doubles(const Process& pr);
 // Whether the eval kernel is launched with one workgroup per compute unit and loops over the points.
 bool pair_persistent(const Process& pr);
+// Threads per workgroup of the eval kernel.
+int pair_block(const Process& pr);
 // Waves per SIMD the body's registers and LDS are laid out for.
 int pair_waves(const Process& pr);
 

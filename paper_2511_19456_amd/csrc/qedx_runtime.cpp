@@ -463,7 +463,7 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
     src = pair ? emit_pair_kernel(proc, v, kname, &st)
                : coop ? emit_coop_kernel(proc, v, kname, &st) : emit_eval_kernel(d, v, kname, &st);
     info.lanes_per_point = pair ? 2 : coop ? coop_lanes(proc) : lanes_per_point(v);
-    info.block = coop ? kCoopBlock : v.block;
+    info.block = coop ? kCoopBlock : v.prec == PREC_F64 && pair_kernel(proc, v) ? pair_block(proc) : v.block;
     info.create_ms_emit = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     info.n_V = st.n_V;
     info.n_S1 = st.n_S1;
