@@ -237,6 +237,11 @@ std::string pair_module_source() {
     // loaded while this one's are worked on
     os << "static __device__ __forceinline__ void qedx_run_" << n
        << "(const qedx_seg& sg, long long p0, long long rounds, double* __restrict__ lds)\n{\n";
+    if (pair_persistent(pr)) {
+      os << "  const long long end = p0 + 32 * rounds;\n  " << b
+         << "_tiles(sg.mom, sg.hel, sg.N, sg.out, p0, 32, end < sg.N ? end : sg.N, lds);\n}\n";
+      continue;
+    }
     os << "  long long pt = p0 + (__lane_id() >> 1);\n";
     os << "  " << b << "_in cur;\n  " << b << "_load(sg.mom, sg.hel, sg.N, pt < sg.N ? pt : sg.N - 1, cur);\n";
     os << "  while (true) {\n    const bool more = --rounds > 0;\n    const long long nx = pt + 32;\n";
@@ -255,7 +260,7 @@ std::string pair_module_source() {
   }
   auto kernel = [&](const std::string& name, int lo, int hi, int waves) {
     int W = 0;
-    for (int n = lo; n <= hi; ++n) W = std::max(W, pair_lds_doubles(Process::make(n, 1)));
+    for (int n = lo; n <= hi; ++n) W = std::max({W, pair_lds_doubles(Process::make(n, 1)), pair_in_doubles(Process::make(n, 1))});
     os << "extern \"C\" __global__ void __launch_bounds__(256, " << waves << ")\n" << name
        << "(const qedx_seg* __restrict__ segs, int nseg, const long long* __restrict__ cut, int chunk)\n{\n";
     if (W) os << "  __shared__ double2 qx_lds[" << 2 * W << "];\n";

@@ -63,16 +63,35 @@ struct Body {
     auto it = slot.find(m);
     return it == slot.end() ? J(m) : "qx::cur_get((const double2*)lds + (go + " + std::to_string(256 * it->second) + "))";
   }
+  // J = S(Q) X.  One current after the other where they fill the registers:
+  // the scheduler, waiting for 1/D, keeps several under way and spills (6
+  // photons 478 us without the barriers, 350 with them).  With 7 photons the
+  // coefficients are divided by D instead, which keeps less under way than the
+  // undivided current (62 instead of 87 registers spilled in the batch kernel,
+  // the n = 1..6 batch 788 instead of 828 us).
   void current(uint32_t m) {
     vertices(m, "X" + std::to_string(m));
-    prop(m, J(m), "X" + std::to_string(m));
+    const std::string n = std::to_string(m);
+    if (pr.P >= 7) {
+      os << "  qx::sp4<double> " << J(m) << ";\n  {\n";
+      K(m, "K");
+      os << "  " << J(m) << " = qx::sL<double>(X" << n << ", qx::prop_from<double>(pe0, pe1, pe2, pe3, K0, K1, K2, K3, sd, 1.0));\n  }\n";
+      st.flops_per_point += 28 + 56;
+      ++st.n_prop;
+      ++st.n_S1;
+    } else {
+      prop(m, "Y" + n, "X" + n, "i" + n);
+      os << "  const qx::sp4<double> " << J(m) << " = qx::scaled<double>(Y" << n << ", i" << n << ");\n";
+      st.flops_per_point += 8;
+    }
+    if (pr.P >= 6) os << "  __builtin_amdgcn_sched_barrier(0);\n";
   }
-  // Y = S(Q) X
-  void prop(uint32_t m, const std::string& Y, const std::string& X) {
-    os << "  qx::sp4<double> " << Y << ";\n  {\n";
+  // Y = D S(Q) X, i = 1/D
+  void prop(uint32_t m, const std::string& Y, const std::string& X, const std::string& i) {
+    os << "  qx::sp4<double> " << Y << ";\n  double " << i << ";\n  {\n";
     K(m, "K");
-    os << "  " << Y << " = qx::sL<double>(" << X << ", qx::prop_from<double>(pe0, pe1, pe2, pe3, K0, K1, K2, K3, sd, 1.0));\n  }\n";
-    st.flops_per_point += 28 + 56;
+    os << "  " << Y << " = qx::prop_num<double>(" << X << ", pe0, pe1, pe2, pe3, K0, K1, K2, K3, sd, " << i << ");\n  }\n";
+    st.flops_per_point += 28 + 48;
     ++st.n_prop;
     ++st.n_S1;
   }
@@ -113,10 +132,10 @@ struct Body {
       os << "    const qx::pol3<double> o = qx::pol<double>(q ? k" << a + 1 << "_1 : k" << a << "_1, q ? k" << a + 1
          << "_2 : k" << a << "_2, q ? k" << a + 1 << "_3 : k" << a << "_3, (int)((hc >> (q ? "
          << pr.photon_particle[a + 1] << "u : " << pr.photon_particle[a] << "u)) & 1u));\n";
-      os << "    const qx::pol3<double> p = {qx::lane_xor1(o.e1), qx::lane_xor1(o.e2), qx::lane_xor1(o.e3)};\n";
-      os << "    e" << a << ".e1 = q ? p.e1 : o.e1; e" << a << ".e2 = q ? p.e2 : o.e2; e" << a << ".e3 = q ? p.e3 : o.e3;\n";
-      os << "    e" << a + 1 << ".e1 = q ? o.e1 : p.e1; e" << a + 1 << ".e2 = q ? o.e2 : p.e2; e" << a + 1
-         << ".e3 = q ? o.e3 : p.e3;\n  }\n";
+      for (int i = 0; i < 2; ++i)
+        for (int c = 1; c < 4; ++c)
+          os << "    e" << a + i << ".e" << c << " = qx::lane_of_pair<" << i << ">(o.e" << c << ");\n";
+      os << "  }\n";
       st.flops_per_point += 16;
     }
     if (P % 2) {
@@ -154,9 +173,9 @@ struct Body {
         vertices(full & ~m, "C");
         os << "  const qx::sp4<double> R = qx::lane_xor1(C);\n";
         vertices(m, "X");
-        prop(m, "Y", "X");
-        os << "  qx::pair_acc<double>(A, R, Y);\n  }\n";
-        st.flops_per_point += 32;
+        prop(m, "Y", "X", "i");
+        os << "  qx::cx<double> B = {0.0, 0.0};\n  qx::pair_acc<double>(B, R, Y);\n  A.r += i * B.r;\n  A.i += i * B.i;\n  }\n";
+        st.flops_per_point += 36;
         ++st.n_dot;
       }
     } else {
@@ -209,6 +228,8 @@ struct Body {
 
 int pair_lds_doubles(const Process& pr) { return pr.P >= 7 ? 512 * kSlots + 32 * 4 * pr.P : 0; }
 
+int pair_in_doubles(const Process& pr) { return pair_persistent(pr) ? 32 * (4 * pr.npart + 1) : 0; }
+
 int pair_waves(const Process& pr) { return pr.P >= 5 ? 1 : 2; }
 
 // 7 photons: a workgroup of four waves would hold the whole LDS until its last
@@ -234,12 +255,40 @@ std::string emit_pair_body(const Process& pr, const std::string& fname, EmitStat
   for (int a = 0; a < pr.P; ++a)
     os << "    in.k[" << a << "][mu] = pk[(" << 4 * pr.photon_particle[a] << " + mu) * N];\n";
   os << "  }\n}\n";
+  if (pair_persistent(pr)) {
+    const int R = 4 * pr.npart;
+    os << "static __device__ __forceinline__ void " << fname
+       << "_fetch(const double* __restrict__ mom, const unsigned* __restrict__ hel, long long N, long long p0, double* buf)\n{\n"
+       << "  const long long first = p0 < N ? p0 : N - 1;\n  const unsigned left = N - 1 - first < 31 ? (unsigned)(N - 1 - first) : 31u;\n"
+       << "  const unsigned i = __lane_id() >> 1, j = __lane_id() & 31u;\n"
+       << "  const unsigned at = 8u * (i < left ? i : left) + 4u * (__lane_id() & 1u);\n  const char* row = (const char*)(mom + first);\n"
+       << "#pragma unroll 4\n  for (int r = 0; r < " << R << "; ++r, row += 8 * N) qx::to_lds(row, at, buf + 32 * r);\n"
+       << "  qx::to_lds((const char*)(hel + first), 4u * (j < left ? j : left), buf + " << 32 * R << ");\n}\n";
+    os << "static __device__ __forceinline__ void " << fname << "_take(const double* buf, " << fname << "_in& in)\n{\n"
+       << "  const unsigned g = __lane_id() >> 1, e = (__lane_id() & 1u) ? " << 128 * pr.i_eout << "u + g : " << 128 * pr.i_ein
+       << "u + g;\n  in.hel = ((const unsigned*)(buf + " << 32 * R << "))[g];\n"
+       << "#pragma unroll\n  for (int mu = 0; mu < 4; ++mu) {\n    in.pe[mu] = buf[e + 32 * mu];\n";
+    for (int a = 0; a < pr.P; ++a)
+      os << "    in.k[" << a << "][mu] = buf[g + " << 128 * pr.photon_particle[a] << " + 32 * mu];\n";
+    os << "  }\n}\n";
+  }
   os << "static __device__ __forceinline__ double " << fname << "_run(const " << fname
      << "_in& in, double* __restrict__ lds)\n{\n" << b.os.str() << "}\n";
   os << "static __device__ __forceinline__ double " << fname
      << "(const double* __restrict__ mom, const unsigned* __restrict__ hel, long long N, long long pt, double* "
         "__restrict__ lds)\n{\n  " << fname << "_in in;\n  " << fname << "_load(mom, hel, N, pt, in);\n  return " << fname
      << "_run(in, lds);\n}\n";
+  if (!pair_persistent(pr)) return os.str();
+  os << "static __device__ __forceinline__ void " << fname
+     << "_tiles(const double* __restrict__ mom, const unsigned* __restrict__ hel, long long N, double* __restrict__ out, long long p0, "
+        "long long step, long long end, double* __restrict__ buf)\n{\n";
+  os << "  if (p0 >= end) return;\n  qx::lds_taken();\n  " << fname << "_fetch(mom, hel, N, p0, buf);\n";
+  os << "  long long last = -1;\n  double r = 0.0;\n  while (true) {\n    " << fname << "_in in;\n    qx::lds_arrived();\n    " << fname
+     << "_take(buf, in);\n    qx::lds_taken();\n";
+  os << "    const long long nx = p0 + step;\n    if (nx < end) " << fname << "_fetch(mom, hel, N, nx, buf);\n";
+  os << "    if (last >= 0 && last < N && (__lane_id() & 1u) == 0u) out[last] = r;\n    __builtin_amdgcn_sched_barrier(0);\n";
+  os << "    r = " << fname << "_run(in, nullptr);\n    last = p0 + (__lane_id() >> 1);\n    if (nx >= end) break;\n    p0 = nx;\n  }\n";
+  os << "  if (last < N && (__lane_id() & 1u) == 0u) out[last] = r;\n}\n";
   return os.str();
 }
 
@@ -255,18 +304,12 @@ std::string emit_pair_kernel(const Process& pr, const Variant& v, const std::str
      << "(const double* __restrict__ mom, const unsigned* __restrict__ hel, long long N, double* __restrict__ out)\n{\n";
   if (W) os << "  __shared__ double2 qx_lds[" << B / 64 * W / 2 << "];\n";
   const std::string lds = W ? "(double*)qx_lds + (threadIdx.x >> 6) * " + std::to_string(W) : std::string("nullptr");
-  os << "  long long pt = ((long long)blockIdx.x * " << B << " + threadIdx.x) >> 1;\n";
   if (pair_persistent(pr)) {
-    // one wave per SIMD: the next points' inputs are loaded while this one's are worked on
-    os << "  const long long step = 128LL * gridDim.x;\n";
-    os << "  " << body << "_in cur;\n  " << body << "_load(mom, hel, N, pt < N ? pt : N - 1, cur);\n";
-    os << "  while (true) {\n    const long long nx = pt + step;\n    " << body << "_in nin;\n";
-    os << "    " << body << "_load(mom, hel, N, nx < N ? nx : N - 1, nin);\n";
-    os << "    __builtin_amdgcn_sched_barrier(0);\n";
-    os << "    const double r = " << body << "_run(cur, " << lds << ");\n";
-    os << "    if (pt < N && (threadIdx.x & 1u) == 0u) out[pt] = r;\n";
-    os << "    if (nx - (long long)(threadIdx.x >> 1) >= N) break;\n    pt = nx;\n    cur = nin;\n  }\n}\n";
+    os << "  __shared__ double qx_in[4][" << pair_in_doubles(pr) << "];\n";
+    os << "  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n";
+    os << "  " << body << "_tiles(mom, hel, N, out, (long long)blockIdx.x * 128 + 32 * wave, 128LL * gridDim.x, N, qx_in[wave]);\n}\n";
   } else {
+    os << "  const long long pt = ((long long)blockIdx.x * " << B << " + threadIdx.x) >> 1;\n";
     os << "  const double r = " << body << "(mom, hel, N, pt < N ? pt : N - 1, " << lds << ");\n";
     os << "  if (pt < N && (threadIdx.x & 1u) == 0u) out[pt] = r;\n}\n";
   }

@@ -11,21 +11,24 @@
 // partitions on each lane, which hands its partner one current per pair of
 // partitions (DPP lane swap).
 //
-// Bound by FP64 vector instructions: 1.1 (4 photons) to 12.3 (7 photons)
-// thousand per lane, 0.85-0.9 of them FP64 arithmetic, against 3626 to 283306
+// Bound by FP64 vector instructions: 1.1 (4 photons) to 12.1 (7 photons)
+// thousand per lane, 0.75-0.85 of them FP64 arithmetic, against 3626 to 283306
 // FLOPs of the graph that keeps the orderings apart.  Two lanes, because one
 // lane's registers hold one side's currents (P = 6: 15 of 8 doubles) and not
 // both.  They stay in registers up to 6 photons (vector and accumulation
 // registers, one wave per SIMD): kept in LDS instead, 8 of the 15 took 408 us
 // where the registers take 361 (2^20 points, P = 6).  One wave per SIMD hides
-// no load, so P = 5, 6 loop over the points and load the next ones' momenta
-// while they work (P = 6 without: 445 us; P = 5: 169 against 181 us); P <= 4
-// fits 2 to 8 waves per SIMD and is faster in one pass (P = 4: 75 against 88
-// us).  P = 7 has no registers left for that: its three-photon currents with
-// the last photon go to LDS, the others are built where the join needs them.
-// Against one product per ordering (2^20 points): P = 5 418 -> 169 us, P = 6
-// 1421 -> 361 us; P = 7, 100003 points with their phase space, 874 -> 143 us;
-// the mixed n = 1..6 batch of 2.77 M points 4.62 -> 1.08 ms.
+// no load, so P = 5, 6 loop over the points and copy the next ones' momenta
+// into LDS while they work, which takes no register (P = 6: 445 us without
+// loading ahead, 375 us into registers, 349 us into LDS; P = 5: 181, 169 and
+// 162 us); P <= 4 fits 2 to 8 waves per SIMD and is faster in one pass (P = 4:
+// 75 against 88 us).  P = 7 has no LDS left for that: its three-photon
+// currents with the last photon go there, the others are built where the join
+// needs them.
+// Against one product per ordering (2^20 points): P = 5 418 -> 162 us, P = 6
+// 1421 -> 349 us; P = 7, 100003 points with their phase space, 874 -> 144 us;
+// the mixed n = 1..6 batch of 2.77 M points 4.62 -> 0.79 ms.  VALU busy: P = 5
+// 88 %, P = 6 93 %, P = 7 67 %.
 #pragma once
 
 #include <string>
@@ -48,8 +51,13 @@ inline bool pair_kernel(const Process& pr, const Variant& v) { return v.subset &
 // point's |A|^2.  lds: the wave's region of pair_lds_doubles() doubles, 16-byte aligned.
 std::string emit_pair_body(const Process& pr, const std::string& fname, EmitStats* st);
 int pair_lds_doubles(const Process& pr);
-// Whether the eval kernel is launched with one workgroup per compute unit and loops over the points.
+// Whether the eval kernel is launched with one workgroup per compute unit and
+// its waves loop over the points, by the function
+//   void <fname>_tiles(mom, hel, N, out, long long p0, long long step, long long end, double* buf):
+// the wave's points are the 32 from p0 on, p0 + step, ... below end; buf: the
+// wave's LDS for the inputs under way, pair_in_doubles() doubles.
 bool pair_persistent(const Process& pr);
+int pair_in_doubles(const Process& pr);
 // Threads per workgroup of the eval kernel.
 int pair_block(const Process& pr);
 // Waves per SIMD the body's registers and LDS are laid out for.

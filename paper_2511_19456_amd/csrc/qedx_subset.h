@@ -41,6 +41,33 @@ template <class T> QEDX_HD void pair_acc(cx<T>& acc, const sp4<T>& X, const sp4<
   acc.r = r;
   acc.i = i;
 }
+// Propagator of the electron p with the photons K (s = 1: Q = p + K, s = -1:
+// p - K) in units of m: the column (Q-slash + 1) X, without its factor 1/D
+// where one scalar can take it.  Q-slash X adds to X, so no coefficient is
+// divided by D: 24 FMAs and 8 multiplications with 1/D.
+template <class T> QEDX_HD sp4<T> prop_num(const sp4<T>& X, T p0, T p1, T p2, T p3, T K0, T K1, T K2, T K3, T s, T& id) {
+  const T pK = p0 * K0 - p1 * K1 - p2 * K2 - p3 * K3;
+  const T KK = K0 * K0 - K1 * K1 - K2 * K2 - K3 * K3;
+  id = rcp(2.0 * s * pK + KK);
+  const T Q0 = p0 + s * K0, Q1 = p1 + s * K1, Q2 = p2 + s * K2, Q3 = p3 + s * K3, qm = Q0 - Q3, qp = Q0 + Q3;
+  const cx<T>&L0 = X.c[0], &L1 = X.c[1], &R0 = X.c[2], &R1 = X.c[3];
+  sp4<T> o;
+  o.c[0].r = L0.r + qm * R0.r - Q1 * R1.r - Q2 * R1.i;
+  o.c[0].i = L0.i + qm * R0.i - Q1 * R1.i + Q2 * R1.r;
+  o.c[1].r = L1.r - Q1 * R0.r + Q2 * R0.i + qp * R1.r;
+  o.c[1].i = L1.i - Q1 * R0.i - Q2 * R0.r + qp * R1.i;
+  o.c[2].r = R0.r + qp * L0.r + Q1 * L1.r + Q2 * L1.i;
+  o.c[2].i = R0.i + qp * L0.i + Q1 * L1.i - Q2 * L1.r;
+  o.c[3].r = R1.r + Q1 * L0.r - Q2 * L0.i + qm * L1.r;
+  o.c[3].i = R1.i + Q1 * L0.i + Q2 * L0.r + qm * L1.i;
+  return o;
+}
+template <class T> QEDX_HD sp4<T> scaled(const sp4<T>& X, T f) {
+  sp4<T> o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o.c[k] = {X.c[k].r * f, X.c[k].i * f};
+  return o;
+}
 // A row adjoint in the column form of its electron line: (-w1, w0, -w3, w2).
 template <class T> QEDX_HD sp4<T> as_column(const sp4<T>& w) {
   sp4<T> o;
@@ -108,6 +135,23 @@ template <int D> __device__ inline propq<double> prop_at(const double2* p) {
   const double2 a = p[0], b = p[D];
   return {a.x, a.y, b.x, b.y, p[2 * D].x};
 }
+// The value of the even (0) or odd (1) lane of a pair, on both.
+template <int I> __device__ inline double lane_of_pair(double x) {
+  const long long v = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)v, I ? 0xF5 : 0xA0, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), I ? 0xF5 : 0xA0, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, (long long)(unsigned)lo | (long long)hi << 32);
+}
+// Copies a dword per lane, at offset `at` from a uniform address, to 256 bytes
+// of LDS without a register.  The wave
+// waits for the copies with lds_arrived() and, before the next ones, for its
+// own reads with lds_taken().
+__device__ inline void to_lds(const char* src, unsigned at, double* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned*)(src + at),
+                                   (__attribute__((address_space(3))) unsigned*)dst, 4, 0, 0);
+}
+__device__ inline void lds_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ inline void lds_taken() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // Orders the wave's LDS accesses (the hardware keeps them in program order).
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
