@@ -9,9 +9,10 @@ of the whole batch by qed_eval (momentum load, external states, vertices,
 propagators, joins, diagram sum, |A|^2 and helicity sum).
 
 Printed: one JSON line with the throughput, a roofline entry for the eval
-kernel (algorithmic FLOPs = C(DAG) of the node-reduced helicity-summed graph
-per point, against the FP64 vector peak; kernel time from HIP events on the
-launch stream), the CPU oracle timed on a bounded sample on the host cores,
+kernel (FLOPs of the form the kernel evaluates, one current per photon subset
+and one spin of the incoming electron, against the FP64 vector peak; kernel
+time from HIP events on the launch stream; C(DAG) of the node-reduced graph
+beside it), the CPU oracle timed on a bounded sample on the host cores,
 and further legs on the same GPU: the one-photon workload, the FP32-compensated
 forms (with their error against the FP64 kernel), one random configuration per
 point at n = 5, the mixed n = 1..6 batch in one persistent launch against the
@@ -191,12 +192,30 @@ def traffic_entry(code_hash):
         return None
 
 
-def alg_flops(n, mode, rewrite=0):
-    """C(DAG) per point of the graph the kernel evaluates (node-reduced, or
-    node-reduced then distributed when rewrite = 1)."""
+# FLOPs per point of the forms that the FP64 kernels evaluate (add/mul 1, FMA
+# 2), without what a kernel does twice or on idle lanes: one current per photon
+# subset; over all configurations with one spin of the incoming electron (the
+# other half follows from it); the gradient with its reverse sweep, the
+# polarisation vectors' share as one time-like bilinear per vertex.
+FLOPS_PER_POINT = {1: 450, 2: 1170, 3: 2762, 4: 6290, 5: 14074, 6: 31138}
+FLOPS_SUM = {1: 1523, 2: 4315, 3: 13467, 4: 44715}
+FLOPS_GRAD_N4 = 119269
+
+
+def dag_flops(n, mode, rewrite=0):
+    """C(DAG) per point of the node-reduced graph (distributed when rewrite =
+    1), every configuration in it."""
     from paper_2511_19456_amd.qedx import graph_metrics
     mask = (1 << (n + 3)) - 1 if mode == "sum" else 0
     return graph_metrics(n, enum_mask=mask, reduced=2 if rewrite else True)[0]
+
+
+def alg_flops(n, mode, prec="fp64"):
+    """FLOPs per point of the form evaluated: by photon subsets in FP64, the
+    node-reduced graph in FP32C."""
+    if prec == "fp32c":
+        return dag_flops(n, mode)
+    return (FLOPS_SUM if mode == "sum" else FLOPS_PER_POINT)[n]
 
 
 def rel_err_stats(a, b, per_point=False):
@@ -259,7 +278,8 @@ def main():
                    "kernel": info["kernel_tag"], "code_hash": info["code_hash"]},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_VECTOR_PEAK_TFLOPS, "traffic": traffic_entry(info["code_hash"]),
-                     "flops_per_point": flops_pt, "kernel": info["kernel_name"],
+                     "flops_per_point": flops_pt, "c_dag_flops_per_point": dag_flops(n, "sum"),
+                     "kernel": info["kernel_name"],
                      "executed_flops_per_point": info["flops_per_point"]},
     }
     ref_n3 = out.clone()
@@ -307,7 +327,7 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
         p = QedProcess(3, "sum", "fp32c")
         o = torch.empty(N, dtype=torch.float64, device=dev)
         ms = time_launches(lambda: p.eval(mom_n3, out=o), steps, 2)
-        r = rate(ms, N, alg_flops(3, "sum"), FP32_VECTOR_PEAK_TFLOPS)
+        r = rate(ms, N, alg_flops(3, "sum", "fp32c"), FP32_VECTOR_PEAK_TFLOPS)
         r["err_vs_fp64_kernel"] = rel_err_stats(o, ref_n3)
         return r
     _leg(legs, "n3_sum_fp32c_2p20", want, n3_fp32c)
@@ -325,18 +345,18 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
             o1 = torch.empty(N, dtype=torch.float64, device=dev)
             ms0 = time_launches(lambda: base.eval(m, hd, out=o0), steps, 2)
             ms1 = time_launches(lambda: dist.eval(m, hd, out=o1), steps, 2)
-            r = rate(ms1, N, alg_flops(n, mode, rewrite=1), FP64_VECTOR_PEAK_TFLOPS)
-            r.update({"ms_node_reduced_only": ms0, "speedup_vs_node_reduced": ms0 / ms1,
-                      "rel_diff_vs_node_reduced": rel_err_stats(o1, o0, per_point=(mode == "per_point")),
+            r = rate(ms1, N, alg_flops(n, mode), FP64_VECTOR_PEAK_TFLOPS)
+            r.update({"ms_default_variant": ms0, "speedup_vs_default_variant": ms0 / ms1,
+                      "rel_diff_vs_default_variant": rel_err_stats(o1, o0, per_point=(mode == "per_point")),
                       "kernel": dist.info()["kernel_name"]})
             return r
         return run
     _leg(legs, "n3_sum_fp64_distributive_2p20", want, distributive(3, "sum", 10.0, 2))
 
     def mfma_join():
-        """The same distributive n = 3 helicity-sum graph with its joins (4 x 4
+        """The distributive n = 3 helicity-sum graph with its joins (4 x 4
         complex dot blocks per photon partition) on the FP64 matrix cores,
-        against its vector joins, on the headline points."""
+        against the kernel without joins, on the headline points."""
         from paper_2511_19456_amd.qedx import make_variant
         N = ref_n3.numel()
         vec = QedProcess(3, "sum", "fp64", make_variant(rewrite=1))
@@ -345,11 +365,10 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
         o1 = torch.empty(N, dtype=torch.float64, device=dev)
         ms0 = time_launches(lambda: vec.eval(mom_n3, out=o0), steps, 2)
         ms1 = time_launches(lambda: mat.eval(mom_n3, out=o1), steps, 2)
-        fl = alg_flops(3, "sum", rewrite=1)
-        r = rate(ms1, N, fl, FP64_VECTOR_PEAK_TFLOPS)
+        r = rate(ms1, N, dag_flops(3, "sum", rewrite=1), FP64_VECTOR_PEAK_TFLOPS)
         i0, i1 = vec.info(), mat.info()
-        r.update({"ms_vector_join": ms0, "speedup_vs_vector_join": ms0 / ms1,
-                  "rel_diff_vs_vector_join": rel_err_stats(o1, o0), "kernel": i1["kernel_name"],
+        r.update({"ms_vector": ms0, "speedup_vs_vector": ms0 / ms1,
+                  "rel_diff_vs_vector": rel_err_stats(o1, o0), "kernel": i1["kernel_name"],
                   "vgpr_agpr_scratch": [i1["vgpr"], i1["agpr"], i1["scratch_bytes"]],
                   "vector_vgpr_agpr_scratch": [i0["vgpr"], i0["agpr"], i0["scratch_bytes"]]})
         return r
@@ -369,7 +388,7 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
             m = p.rambo(torch.as_tensor(u5, device=dev), wl5["sqrt_s"])
             o = torch.empty(wl5["N"], dtype=torch.float64, device=dev)
             ms = time_launches(lambda: p.eval(m, h5d, out=o), steps, 2)
-            r = rate(ms, wl5["N"], alg_flops(5, "per_point"),
+            r = rate(ms, wl5["N"], alg_flops(5, "per_point", prec),
                      FP64_VECTOR_PEAK_TFLOPS if prec == "fp64" else FP32_VECTOR_PEAK_TFLOPS)
             p5[prec + "_out"] = o
             info = p.info()
@@ -401,7 +420,7 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
                 hd = torch.as_tensor(h.astype(np.int32), device=dev)
                 o = torch.empty(Np, dtype=torch.float64, device=dev)
                 segs.append((p, m, hd, o))
-                tot_flops += alg_flops(n, "per_point") * Np
+                tot_flops += alg_flops(n, "per_point", prec) * Np
                 tot_pts += Np
             torch.cuda.synchronize()
             t0 = time.perf_counter()
@@ -522,20 +541,15 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
             p.rambo(ud, wl["sqrt_s"], out=m)
             p.eval(m, out=o)
         ms_f = time_launches(fwd, steps, 2)
-        # algorithmic FLOPs: forward C(DAG) of the node-reduced helicity-sum
-        # graph plus the reverse-mode cost of the same graph (per-node
-        # vector-Jacobian products); RAMBO and its adjoint are HBM-side and
-        # not counted
-        from paper_2511_19456_amd.qedx import graph_adjoint_metrics
-        c_f, c_a = graph_adjoint_metrics(wl["n"], enum_mask=(1 << (wl["n"] + 3)) - 1)
-        achieved = (c_f + c_a) * wl["N"] / (ms * 1e-3) / 1e12
+        # the form evaluated: subset currents and the reverse sweep over them;
+        # RAMBO and its adjoint are not counted
+        achieved = FLOPS_GRAD_N4 * wl["N"] / (ms * 1e-3) / 1e12
         return {"ms": ms, "points_per_s": wl["N"] / (ms * 1e-3), "ms_forward_only": ms_f,
                 "grad_over_forward": ms / ms_f,
                 "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
                              "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK_TFLOPS,
-                             "flops_per_point": c_f + c_a, "forward_flops_per_point": c_f,
-                             "adjoint_flops_per_point": c_a,
-                             "note": "whole qed_eval_grad call (RAMBO, amplitudes, adjoint sweeps, RAMBO adjoint)"}}
+                             "flops_per_point": FLOPS_GRAD_N4, "forward_flops_per_point": FLOPS_SUM[4],
+                             "note": "whole qed_eval_grad call (RAMBO, currents and reverse sweep, RAMBO adjoint)"}}
     _leg(legs, "grad_n4_sum_fp64_2p18", want, grad)
 
     def table1_crossed():
@@ -551,8 +565,7 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
             o = torch.empty(N, dtype=torch.float64, device=dev)
             ms = time_launches(lambda: p.eval(md, hd, out=o), steps, 2)
             inf = p.info()
-            from paper_2511_19456_amd.qedx import graph_metrics
-            fl = graph_metrics(1, n_in=n_in, reduced=True)[0]   # C(DAG), one configuration
+            fl = FLOPS_PER_POINT[n_in]   # by photon subsets; the photon count decides, not which are incoming
             t = fl * N / (ms * 1e-3) / 1e12
             rows.append({"n": n_in, "ms": ms, "ns_per_point": ms * 1e6 / N, "points_per_s": N / (ms * 1e-3),
                          "nodes_unreduced": inf["nodes_unreduced"], "nodes_reduced": inf["nodes_reduced"],

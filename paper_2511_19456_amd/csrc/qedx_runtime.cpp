@@ -259,6 +259,11 @@ static qed_status get_code_object(const std::string& tag, const std::string& src
 // processes
 // ---------------------------------------------------------------------------
 
+// FP64 processes without an explicit shape are evaluated by photon subsets
+// (per point: qedx_pair.hpp, helicity sums of up to 5 photons: qedx_coop.hpp)
+// and keep of the shape chosen here only the name.  It is the shape of FP32C
+// kernels, of helicity sums of more photons and, where an explicit variant
+// leaves a field open, of that variant; the figures are of these graph kernels.
 static void default_variant(int n, int nin, qed_hel_mode mode, qed_precision prec, int rewrite, Variant& v) {
   v = Variant();
   v.prec = prec == QED_FP64 ? PREC_F64 : PREC_F32C;
