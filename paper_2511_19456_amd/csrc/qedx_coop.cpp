@@ -506,7 +506,8 @@ struct Coop {
 
 // Measured, 2^20 points (99991 at 5 photons), us for 4 / 8 / 16 / 32 lanes:
 // 2 photons 50 / 97 / 173 / -, 3 photons 149 / 167 / 260 / -, 4 photons 642 /
-// 446 / 510 / -, 5 photons 700 / 323 / 190 / 174.  Fewer lanes need more LDS
+// 446 / 510 / - (435 with the points' offsets of today), 5 photons 700 / 323 /
+// 190 / 174.  Fewer lanes need more LDS
 // per wave than leaves two waves per SIMD, more lanes idle in the levels with
 // few items.
 int coop_lanes(const Process& pr) { return pr.P == 5 ? 32 : pr.P == 4 ? 8 : 4; }

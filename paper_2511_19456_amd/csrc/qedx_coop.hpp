@@ -15,8 +15,9 @@
 // lane at 4 photons, 1.55 at 5) and LDS reads (a vertex reads 88 bytes per lane
 // for 24 instructions, 0.9 of the time its instructions take).  Measured
 // against the kernels with one product per ordering, both spins and the joins
-// (2^20 points): 4 photons 1.61 -> 0.45 ms (VALU busy 0.66), 3 photons 407 ->
-// 149 us, 2 photons 98 -> 50 us; 5 photons, 99991 points, 2.52 -> 0.174 ms.
+// (2^20 points): 4 photons 1.61 -> 0.435 ms (VALU busy 0.67, LDS 0.48), 3
+// photons 407 -> 149 us, 2 photons 98 -> 50 us; 5 photons, 99991 points, 2.52 ->
+// 0.170 ms (0.74, 0.53).
 #pragma once
 
 #include <string>
@@ -40,14 +41,14 @@ std::string emit_coop_kernel(const Process& pr, const Variant& v, const std::str
 // the same levels downwards with the adjoints in the currents' LDS slots; each
 // lane keeps the currents of its own items in registers (14 of them at 5
 // photons), so nothing is recomputed and LDS stays what the forward needs.  The
-// sums over items (40 polarisation and momentum gradients at 5 photons) are per
-// lane in registers and meet in LDS once, at the end.  At 5 photons 456
-// registers leave one wave per SIMD: VALU busy 0.58 of the time, LDS reads
-// take 0.43 of it (a third of that bank conflicts).  Measured against one walk
-// over the orderings per partition and electron: 5 photons, 2^18 points, 14.2 ->
-// 1.51 ms (16 lanes per point; 32 lanes 2.29); 4 photons, 2^19 points, 48.6 ->
-// 0.98 ms (a wave per SIMD instead of two, without 24 spilled registers: 1.26);
-// 3 photons 7.25 -> 0.34 ms, 2 photons 1.15 -> 0.21 ms.  With rambo: through the
+// sums over items (28 polarisation and momentum gradients at 5 photons) are per
+// lane in registers and meet in LDS once, at the end.  At 5 photons 468
+// registers leave one wave per SIMD: VALU busy 0.56 of the time, LDS 0.40 (a
+// fifth of that bank conflicts), 0.20 waits.  Measured against one walk over
+// the orderings per partition and electron: 5 photons, 2^18 points, 14.2 -> 1.32
+// ms (16 lanes per point; with 32 2.29 when 16 took 1.56); 4 photons, 2^19
+// points, 48.6 -> 0.79 ms (one wave per SIMD instead of two 1.26 when two took
+// 0.98); 3 photons 7.25 -> 0.28 ms, 2 photons 1.15 -> 0.16 ms.  With rambo: through the
 // phase-space map,
 //   <kname>(const double* u, double sqrt_s, long long N, double* logm2, double* grad, int tiles),
 // one wave per `tiles` (1 .. 64 / points of a wave) groups of points; without:
