@@ -74,16 +74,19 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   // run 2 or 4 lanes per point and keep the cache in their wave's region of
   // qx_cache_mem.
   // FP64 processes without an explicit kernel shape take the pair bodies (two
-  // lanes per point).
-  std::vector<char> pol(procs.size(), 0), cache(procs.size(), 0), cache64(procs.size(), 0), pair(procs.size(), 0);
+  // lanes per point; pair), and so does the FP64 pass of such FP32C processes
+  // (pair64).
+  std::vector<char> pol(procs.size(), 0), cache(procs.size(), 0), cache64(procs.size(), 0), pair(procs.size(), 0),
+      pair64(procs.size(), 0);
   os << subset_header_text() << "\n";
   int pol_npart = 0, cache_w = 0, cache_w64 = 0;
   for (size_t i = 0; i < procs.size(); ++i) {
     Dag d = graph_for(procs[i].first, procs[i].second, nullptr, nullptr);
     EmitStats st;
     const Process& pr = procs[i].first;
-    pair[i] = pair_kernel(pr, procs[i].second);
-    if (pair[i] && !fix) {
+    pair[i] = pair_eval(pr, procs[i].second);
+    pair64[i] = fix && pair_kernel(pr, procs[i].second);
+    if (pair[i]) {
       cache_w = std::max(cache_w, pair_lds_doubles(pr));
       os << emit_pair_body(pr, "qedx_body_" + std::to_string(i), &st) << "\n";
       continue;
@@ -98,7 +101,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
       Variant v64 = procs[i].second;
       v64.prec = PREC_F64;
       v64.fixup = 0;
-      if (pair[i]) {
+      if (pair64[i]) {
         cache_w64 = std::max(cache_w64, pair_lds_doubles(pr));
         os << emit_pair_body(pr, "qedx_body64_" + std::to_string(i), &st) << "\n";
         continue;
@@ -137,7 +140,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   if (fix) os << "      int ff = 0;\n";
   os << "      switch (sg.proc) {\n";
   for (size_t i = 0; i < procs.size(); ++i)
-    if (pair[i] && !fix)
+    if (pair[i])
       os << "        case " << i << ": r = qedx_body_" << i << "(sg.mom, sg.hel, sg.N, ptc, "
          << (cache_w ? "(double*)qx_cache_mem + (threadIdx.x >> 6) * " + std::to_string(cache_w) : "nullptr") << "); break;\n";
     else
@@ -188,7 +191,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
           "      double r = 0.0;\n"
           "      switch (sg.proc) {\n";
     for (size_t i = 0; i < procs.size(); ++i)
-      if (pair[i])
+      if (pair64[i])
         os << "        case " << i << ": r = qedx_body64_" << i << "(sg.mom, sg.hel, sg.N, pt, "
            << (cache_w64 ? "(double*)qx_fc + (threadIdx.x >> 6) * " + std::to_string(cache_w64) : "nullptr") << "); break;\n";
       else
@@ -287,7 +290,7 @@ double tile_cost(double flops_per_point) { return flops_per_point + 1500.0; }
 
 bool all_pair(const std::vector<std::pair<Process, Variant>>& pv) {
   for (auto& p : pv)
-    if (p.second.prec != PREC_F64 || p.first.n_in != 1 || !pair_kernel(p.first, p.second)) return false;
+    if (p.first.n_in != 1 || !pair_eval(p.first, p.second)) return false;
   return true;
 }
 
@@ -519,9 +522,9 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   auto b = std::make_unique<qed_batch_plan>();
   b->nseg = nseg;
   for (auto* p : procs) {
-    const bool pair = pair_kernel(p->proc, p->var);
-    b->shift.push_back(pair && p->prec == QED_FP64 ? 1 : __builtin_ctz(cache_lanes(p->var)));
-    b->shift64.push_back(pair ? 1 : __builtin_ctz(cache_lanes(p->var)));
+    const int graph = __builtin_ctz(cache_lanes(p->var));
+    b->shift.push_back(pair_eval(p->proc, p->var) ? 1 : graph);
+    b->shift64.push_back(pair_kernel(p->proc, p->var) ? 1 : graph);
   }
   // module (cached like every generated unit)
   std::string src;

@@ -42,8 +42,11 @@ namespace qedx {
 // only: a process's eval kernel and the batch kernels give the same bits.
 constexpr const char* kContractOn = "// fp-contract: on\n";
 
-// Whether (process, variant) is evaluated by the pair kernels.
+// Whether (process, variant) takes the pair body in FP64: its eval kernel if
+// it is an FP64 process, else the FP64 pass after its FP32C kernel.
 inline bool pair_kernel(const Process& pr, const Variant& v) { return v.subset && v.mode == HEL_PER_POINT; }
+// Whether its eval kernel does.
+inline bool pair_eval(const Process& pr, const Variant& v) { return v.prec == PREC_F64 && pair_kernel(pr, v); }
 
 // Device function text
 //   static __device__ double <fname>(const double* mom, const unsigned* hel, long long N, long long pt, double* lds)

@@ -462,13 +462,13 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
     info.nodes_reduced = (int64_t)d.nodes.size();
     auto t0 = std::chrono::steady_clock::now();
     EmitStats st;
-    const bool pair = prec == QED_FP64 && pair_kernel(proc, v);
+    const bool pair = pair_eval(proc, v);
     const bool coop = coop_kernel(proc, v);
     const std::string kname = eval_kernel_name(n, nin, mode, prec, v);
     src = pair ? emit_pair_kernel(proc, v, kname, &st)
                : coop ? emit_coop_kernel(proc, v, kname, &st) : emit_eval_kernel(d, v, kname, &st);
     info.lanes_per_point = pair ? 2 : coop ? coop_lanes(proc) : lanes_per_point(v);
-    info.block = coop ? kCoopBlock : v.prec == PREC_F64 && pair_kernel(proc, v) ? pair_block(proc) : v.block;
+    info.block = coop ? kCoopBlock : pair ? pair_block(proc) : v.block;
     info.create_ms_emit = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     info.n_V = st.n_V;
     info.n_S1 = st.n_S1;
@@ -577,7 +577,7 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   int dev = 0, ncu = 256;
   HIPCHK(hipGetDevice(&dev));
   HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  if (prec == QED_FP64 && pair_kernel(p->proc, p->var) && pair_persistent(p->proc)) p->max_groups = ncu;
+  if (pair_eval(p->proc, p->var) && pair_persistent(p->proc)) p->max_groups = ncu;
   if (p->var.fixup) {
     std::string fx = std::string(p->info.kernel_name) + "_fix";
     HIPCHK(hipModuleGetFunction(&p->f_fix, p->mod, fx.c_str()));
