@@ -31,6 +31,7 @@ struct Coop {
 
   // where the momenta are read: row r of the point
   std::string mrow(int r) const { return mom_lds ? "mq[" + std::to_string(64 * (r - 8)) + "u + g]" : "mom[" + std::to_string(r) + " * N + ptc]"; }
+  bool ward = true;      // gradient: see reverse()
   bool mom_lds = false;  // final-state momenta of the wave's 64 points in LDS, incoming ones in pin, kin
 
   Coop(const Process& p, int lanes, bool grad = false) : pr(p), P(p.P), L(lanes), PPW(64 / L) {
@@ -294,7 +295,10 @@ struct Coop {
   // amplitude with k/|k| for eps_lambda, by the Ward identity minus the one
   // with (1, 0, 0, 0): the bilinear of gamma^0, 8 FMAs where the three
   // components of eps take 24 (1510 -> 1360 us for 2^18 points of 5 photons,
-  // 80 -> 71 us for 20011 of 4).
+  // 80 -> 71 us for 20011 of 4).  Near the threshold that response is what is
+  // left when the two electrons' terms cancel (their velocities, v, are all
+  // that tells them apart), and the answer loses 1/v^2: there (ward = false)
+  // the bilinear of k/|k| = eps_0 x eps_1 itself is taken.
   // Leaves the final-state momentum gradients through store().
   void reverse(const std::function<void()>& store) {
     // the bilinears are real parts without their factor 2: the seed carries it
@@ -365,7 +369,10 @@ struct Coop {
     pick_photon();
     // (zero along the z axis, where the vectors themselves have no derivative)
     os << "    const qx::pol3<double> e = qx::pol_at<" << 2 * P << ">(cu + " << pol0 << "u, i);\n";
-    os << "    const double t = x1 * x1 + x2 * x2 > 0.0 ? (rs[i] + qx::bil0(w1, u0)) * qx::rsqrt(x1 * x1 + x2 * x2 + x3 * x3) : 0.0;\n";
+    if (!ward)
+      os << "    const double ik = qx::rsqrt(x1 * x1 + x2 * x2 + x3 * x3);\n    const qx::pol3<double> kh = {x1 * ik, x2 * ik, x3 * ik};\n";
+    os << "    const double t = x1 * x1 + x2 * x2 > 0.0 ? (rs[i] + " << response("w1", "u0")
+       << ") * qx::rsqrt(x1 * x1 + x2 * x2 + x3 * x3) : 0.0;\n";
     os << "    double v[3] = {t * e.e1, t * e.e2, t * e.e3};\n";
     os << "    v[0] += qx::lane_xor1(v[0]);\n    v[1] += qx::lane_xor1(v[1]);\n    v[2] += qx::lane_xor1(v[2]);\n";
     os << "    const double* const q = rs + (" << 2 * P << "u + 4u * a);\n";
@@ -375,6 +382,11 @@ struct Coop {
     store();
     os << "  }\n";
     st.flops_per_point += 250.0 * L;
+  }
+
+  // minus the response to the spatial part of k/|k|, kh
+  std::string response(const std::string& w, const std::string& C) const {
+    return ward ? "qx::bil0(" + w + ", " + C + ")" : "qx_along(kh, qx::bil3(" + w + ", " + C + "))";
   }
 
   // whether the reverse sweep loads a step's operands during the one before:
@@ -426,15 +438,20 @@ struct Coop {
         os << "  __builtin_amdgcn_sched_barrier(0);\n  {\n";
         const std::vector<int>& ph = phs[r * nj + j];
         const std::string g = tag(r, j);
+        const std::string load1 = "      const double2 e1 = cu[" + std::to_string(pol0 + 1) + "u + ph" + g + "];\n";
+        const std::string load0 = "      const qx::pol3<double> e0 = qx::pol_at<" + std::to_string(2 * P) + ">(cu + " +
+                                  std::to_string(pol0) + "u, ph" + g + ");\n";
+        if (!ward)
+          os << load0 << load1
+             << "      const qx::pol3<double> kh = {-e0.e3 * e1.y, e0.e3 * e1.x, e0.e1 * e1.y - e0.e2 * e1.x};\n";
         for (int h = 0; h < 2; ++h) {
           const std::string W = (h ? "v" : "u") + g;
+          if (ward) os << (h ? load1 : load0);
           if (h)  // eps(1) = (-sin phi, cos phi, 0): 1344 -> 1322 us for 2^18 points of 5 photons
-            os << "      const double2 e1 = cu[" << pol0 + 1 << "u + ph" << g << "];\n      qx::vL_add_flat<double>(G" << kr << ", "
-               << W << ", e1.x, e1.y);\n";
+            os << "      qx::vL_add_flat<double>(G" << kr << ", " << W << ", e1.x, e1.y);\n";
           else
-            os << "      const qx::pol3<double> e0 = qx::pol_at<" << 2 * P << ">(cu + " << pol0 << "u, ph" << g << ");\n      "
-               << (j == 0 ? "G" + kr + " = qx::vL<double>(" : "qx::vL_add<double>(G" + kr + ", ") << W << ", e0);\n";
-          os << "      const double b" << h << " = qx::bil0(" << W << ", " << C << ");\n";
+            os << "      " << (j == 0 ? "G" + kr + " = qx::vL<double>(" : "qx::vL_add<double>(G" + kr + ", ") << W << ", e0);\n";
+          os << "      const double b" << h << " = " << response(W, C) << ";\n";
           st.flops_per_point += ((h ? 32.0 : 48.0) + 16) * L;
         }
         std::vector<int> seen;
@@ -534,8 +551,9 @@ int coop_grad_lanes(const Process& pr) {
   return pr.P >= 4 ? 16 : 8;
 }
 
-std::string emit_coop_grad_kernel(const Process& pr, const std::string& kname, bool rambo, EmitStats* st) {
+std::string emit_coop_grad_kernel(const Process& pr, const std::string& kname, bool rambo, bool ward, EmitStats* st) {
   Coop b(pr, coop_grad_lanes(pr), true);
+  b.ward = ward;
   b.mom_lds = rambo;
   if (b.overlay()) throw std::logic_error("coop: the reverse sweep reads the propagators again");
   b.forward();
@@ -556,6 +574,9 @@ std::string emit_coop_grad_kernel(const Process& pr, const std::string& kname, b
   if (st) *st = b.st;
   std::ostringstream os;
   const int LDS = b.PPW * b.PT;
+  if (!ward)
+    os << "static __device__ __forceinline__ double qx_along(const qx::pol3<double>& k, const qx::pol3<double>& b)\n{\n"
+          "  return -(k.e1 * b.e1 + k.e2 * b.e2 + k.e3 * b.e3);\n}\n";
   if (!rambo) {
     os << "extern \"C\" __global__ void __launch_bounds__(64)\n" << kname
        << "(const double* __restrict__ mom, long long N, double* __restrict__ gm, double* __restrict__ logm2)\n{\n";

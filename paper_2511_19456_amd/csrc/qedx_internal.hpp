@@ -31,12 +31,12 @@ struct qed_process {
   hipFunction_t f_fix = nullptr;  // FP64 pass of FP32C per-point kernels (null if none)
   hipModule_t mod_aux = nullptr;  // RAMBO and gradient kernels
   hipFunction_t f_rambo = nullptr;
-  hipFunction_t f_grad = nullptr;
+  hipFunction_t f_grad = nullptr, f_grad_low = nullptr;  // (sqrt(s) below kWardFrom: low)
   int grad_points = 0;  // points of one wave of the gradient kernel
   int max_waves = 0;    // waves the device holds at two per SIMD
   // split gradient (n = 4): kernels; the workspace is the caller's
   int grad_split = 0;
-  hipFunction_t f_grambo = nullptr, f_gmom = nullptr, f_grvjp = nullptr;
+  hipFunction_t f_grambo = nullptr, f_gmom = nullptr, f_gmom_low = nullptr, f_grvjp = nullptr;
   std::string eval_src;
   ~qed_process() {
     // launches are asynchronous: wait for any still running before the

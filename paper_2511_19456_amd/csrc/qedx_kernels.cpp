@@ -36,11 +36,13 @@ std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInf
   ai.grad_points = 64 / coop_grad_lanes(proc);
   if (n <= 3) {
     // fused: RAMBO, currents, reverse sweep and RAMBO adjoint in one kernel
-    os << emit_coop_grad_kernel(proc, "qedx_grad_n" + ns, true, &st);
+    os << emit_coop_grad_kernel(proc, "qedx_grad_n" + ns, true, true, &st);
+    os << emit_coop_grad_kernel(proc, "qedx_grad_low_n" + ns, true, false, &st);
   } else {
     // split: RAMBO into the workspace, the gradient over its momenta, RAMBO adjoint
     ai.split = 1;
-    os << emit_coop_grad_kernel(proc, "qedx_gmom_n" + ns, false, &st);
+    os << emit_coop_grad_kernel(proc, "qedx_gmom_n" + ns, false, true, &st);
+    os << emit_coop_grad_kernel(proc, "qedx_gmom_low_n" + ns, false, false, &st);
     os << "extern \"C\" __global__ void __launch_bounds__(256)\nqedx_grambo_n" << n
        << "(const double* __restrict__ u, long long ldu, double sqrt_s, long long N, double* __restrict__ mom)\n{\n";
     os << "  const long long pt = (long long)blockIdx.x * 256 + threadIdx.x;\n";

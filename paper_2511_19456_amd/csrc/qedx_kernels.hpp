@@ -25,6 +25,7 @@ struct AuxInfo {
 //      qedx_grambo_n<n>(u, ldu, sqrt_s, N, mom)      RAMBO into the workspace,
 //      qedx_gmom_n<n>(mom, N, gm, logm2)             momentum gradient of log |M|^2,
 //      qedx_grvjp_n<n>(u, ldu, sqrt_s, N, gm, grad, ldg)  RAMBO adjoint.
+// qedx_grad_low_n<n>, qedx_gmom_low_n<n>: the same for sqrt(s) below kWardFrom.
 // n >= 5 has RAMBO only.
 std::string emit_aux_module(const Process& proc, const Variant& v, int n, AuxInfo* info);
 

@@ -607,10 +607,14 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   HIPCHK(hipModuleLoadData(&p->mod_aux, aco.data()));
   const std::string ns = std::to_string(n);
   HIPCHK(hipModuleGetFunction(&p->f_rambo, p->mod_aux, ("qedx_rambo_n" + ns).c_str()));
-  if (hipModuleGetFunction(&p->f_grad, p->mod_aux, ("qedx_grad_n" + ns).c_str()) != hipSuccess) p->f_grad = nullptr;
+  if (p->grad_points && !p->grad_split) {
+    HIPCHK(hipModuleGetFunction(&p->f_grad, p->mod_aux, ("qedx_grad_n" + ns).c_str()));
+    HIPCHK(hipModuleGetFunction(&p->f_grad_low, p->mod_aux, ("qedx_grad_low_n" + ns).c_str()));
+  }
   if (p->grad_split) {
     HIPCHK(hipModuleGetFunction(&p->f_grambo, p->mod_aux, ("qedx_grambo_n" + ns).c_str()));
     HIPCHK(hipModuleGetFunction(&p->f_gmom, p->mod_aux, ("qedx_gmom_n" + ns).c_str()));
+    HIPCHK(hipModuleGetFunction(&p->f_gmom_low, p->mod_aux, ("qedx_gmom_low_n" + ns).c_str()));
     HIPCHK(hipModuleGetFunction(&p->f_grvjp, p->mod_aux, ("qedx_grvjp_n" + ns).c_str()));
   }
   p->max_waves = 8 * ncu;
@@ -731,7 +735,7 @@ static qed_status grad_split_chunks(const qed_process* p, const double* uniforms
     void* a1[] = {(void*)&u, (void*)&ldu, (void*)&sqrt_s, (void*)&cnt, (void*)&mom};
     if ((st = launch(p->f_grambo, cnt, 256, stream, a1))) return st;
     void* a2[] = {(void*)&mom, (void*)&cnt, (void*)&gm, (void*)&lg};
-    if ((st = launch(p->f_gmom, cnt * (64 / p->grad_points), 64, stream, a2))) return st;
+    if ((st = launch(sqrt_s < kWardFrom ? p->f_gmom_low : p->f_gmom, cnt * (64 / p->grad_points), 64, stream, a2))) return st;
     void* a4[] = {(void*)&u, (void*)&ldu, (void*)&sqrt_s, (void*)&cnt, (void*)&gm, (void*)&gr, (void*)&ldu};
     if ((st = launch(p->f_grvjp, cnt, 256, stream, a4))) return st;
   }
@@ -916,7 +920,7 @@ qed_status grad_fused(const qed_process* p, const double* uniforms, double sqrt_
   int t = (int)tiles;
   const int64_t per = tiles * p->grad_points;
   void* args[] = {(void*)&uniforms, (void*)&sqrt_s, (void*)&n, (void*)&out_logm2, (void*)&out_grad, (void*)&t};
-  return launch(p->f_grad, (N + per - 1) / per * 64, 64, stream, args);
+  return launch(sqrt_s < kWardFrom ? p->f_grad_low : p->f_grad, (N + per - 1) / per * 64, 64, stream, args);
 }
 qed_status default_process_variant(int n, qed_hel_mode mode, qed_precision prec, int rewrite, qedx::Variant& v) {
   if (!rewrite) return make_variant(n, 1, mode, prec, nullptr, v);
