@@ -175,7 +175,9 @@ qed_status qed_process_info(const qed_process* p, qed_info* out);
  * kernels on `stream`: the FP32 pass writes its results and marks the points
  * it cannot vouch for with a negative value in `out`, the FP64 pass
  * recomputes the marked points in place; `out` holds final values once both
- * have run.  No other memory is used. */
+ * have run.  No other memory is used.  A launch holds fewer than 2^32 threads:
+ * more points than that run as several launches on `stream` (the kernels with
+ * one current per photon subset) or are INVALID_ARG (the others). */
 qed_status qed_eval(const qed_process* p, const double* momenta, const uint32_t* hel, int64_t N, double* out,
                     void* stream);
 

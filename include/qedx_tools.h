@@ -72,6 +72,14 @@ qed_status qed_graph_grad_interpret(int n, int split, int reduced, const double*
 qed_status qed_rambo_vjp_host(int n, const double* u, double sqrt_s, const double* gk, int64_t N, double* mom,
                               double* gu);
 
+/* How qed_eval splits N points of `lanes` threads each, workgroups of `block`
+ * threads, into launches of at most max_threads: their number, and for launch i
+ * the first point and the points it takes (the last launch may repeat points of
+ * the one before).  INVALID_ARG where block is no multiple of lanes, a size is
+ * below 1, max_threads below block, or i is not a launch. */
+qed_status qed_launch_range(int64_t N, int lanes, int block, int64_t max_threads, int64_t i, int64_t* count,
+                            int64_t* first, int64_t* points);
+
 #ifdef __cplusplus
 }
 #endif

@@ -91,6 +91,8 @@ SIGNATURES = {
                                   ctypes.POINTER(c_double)]),
     "qed_graph_adjoint_metrics": (c_int, [c_int, c_uint32, c_int, c_int, ctypes.POINTER(c_double),
                                           ctypes.POINTER(c_double)]),
+    "qed_launch_range": (c_int, [c_int64, c_int, c_int, c_int64, c_int64, ctypes.POINTER(c_int64),
+                                 ctypes.POINTER(c_int64), ctypes.POINTER(c_int64)]),
 }
 
 # the measurement library (include/qedx_probe.h)

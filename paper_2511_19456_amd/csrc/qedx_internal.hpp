@@ -25,6 +25,7 @@ struct qed_process {
   qedx::Process proc;
   qed_info info{};
   int lanes = 1;
+  bool subset = false;     // the eval kernel takes one current per photon subset
   int64_t max_groups = 0;  // eval kernels that loop over the points: largest grid (0: one pass)
   hipModule_t mod = nullptr;
   hipFunction_t f_eval = nullptr;

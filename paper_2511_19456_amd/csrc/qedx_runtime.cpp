@@ -578,6 +578,7 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   HIPCHK(hipGetDevice(&dev));
   HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   if (pair_eval(p->proc, p->var) && pair_persistent(p->proc)) p->max_groups = ncu;
+  p->subset = pair_eval(p->proc, p->var) || coop_kernel(p->proc, p->var);
   if (p->var.fixup) {
     std::string fx = std::string(p->info.kernel_name) + "_fix";
     HIPCHK(hipModuleGetFunction(&p->f_fix, p->mod, fx.c_str()));
@@ -645,11 +646,41 @@ extern "C" qed_status qed_process_info(const qed_process* p, qed_info* out) {
   return QED_OK;
 }
 
+// A launch holds fewer than 2^32 threads.
+static const int64_t kMaxThreads = 0xffffffff;
+
 static qed_status launch(hipFunction_t f, int64_t threads, int block, void* stream, void** args) {
   int64_t grid = (threads + block - 1) / block;
-  if (grid > 0x7fffffff) return fail(QED_ERR_INVALID_ARG, "N too large for one launch");
+  if (grid > kMaxThreads / block) return fail(QED_ERR_INVALID_ARG, "N too large for one launch");
   HIPCHK(hipModuleLaunchKernel(f, (unsigned)grid, 1, 1, (unsigned)block, 1, 1, 0, (hipStream_t)stream, args,
                                nullptr));
+  return QED_OK;
+}
+
+// N points of `lanes` threads each as `count` launches of at most max_threads:
+// launch i takes `points` points from min(i * points, N - points) on.  Several
+// launches take whole workgroups, so that with N as the rows' stride no thread
+// is past its launch's points; the last one ends at N and repeats some of the
+// one before.
+struct LaunchRanges {
+  int64_t count, points;
+};
+static LaunchRanges launch_ranges(int64_t N, int lanes, int block, int64_t max_threads) {
+  const int64_t tile = block / lanes, most = max_threads / block * tile;
+  if (N <= most) return {1, N};
+  const int64_t count = (N + most - 1) / most, share = (N + count - 1) / count;
+  return {count, (share + tile - 1) / tile * tile};
+}
+
+extern "C" qed_status qed_launch_range(int64_t N, int lanes, int block, int64_t max_threads, int64_t i, int64_t* count,
+                                       int64_t* first, int64_t* points) {
+  if (N < 1 || lanes < 1 || block < lanes || block % lanes || max_threads < block || !count || !first || !points)
+    return fail(QED_ERR_INVALID_ARG, "need N >= 1, lanes that divide block, block <= max_threads");
+  const LaunchRanges r = launch_ranges(N, lanes, block, max_threads);
+  if (i < 0 || i >= r.count) return fail(QED_ERR_INVALID_ARG, "no such launch");
+  *count = r.count;
+  *first = std::min(i * r.points, N - r.points);
+  *points = r.points;
   return QED_OK;
 }
 
@@ -667,7 +698,22 @@ extern "C" qed_status qed_eval(const qed_process* p, const double* momenta, cons
     void* args[] = {(void*)&momenta, (void*)&hel, (void*)&n, (void*)&out};
     int64_t threads = N * (int64_t)p->lanes;
     if (p->max_groups) threads = std::min(threads, p->max_groups * (int64_t)p->info.block);
-    return launch(p->f_eval, threads, p->info.block, stream, args);
+    // the subset kernels' lanes (32 per point of 5 photons: 2^27 points) would
+    // bound N below what memory holds
+    if (!p->subset || threads <= kMaxThreads - p->info.block) return launch(p->f_eval, threads, p->info.block, stream, args);
+    const LaunchRanges r = launch_ranges(N, p->lanes, p->info.block, kMaxThreads);
+    const double* const mom0 = momenta;
+    const uint32_t* const hel0 = hel;
+    double* const out0 = out;
+    for (int64_t i = 0; i < r.count; ++i) {
+      const int64_t first = std::min(i * r.points, N - r.points);
+      momenta = mom0 + first;
+      hel = hel0 ? hel0 + first : nullptr;
+      out = out0 + first;
+      qed_status s = launch(p->f_eval, r.points * p->lanes, p->info.block, stream, args);
+      if (s) return s;
+    }
+    return QED_OK;
   }
   // FP32C pass, which marks the points it cannot resolve with a negative
   // value in `out`, then the FP64 pass over those marks (one workgroup per
