@@ -69,7 +69,9 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   // array of the batch kernel (3 npart values per lane), as the eval kernels
   // do; for every slot-loop body it raised the batch kernel's registers into
   // scratch (5.9 against 5.5 ms on the FP64 n = 1..6 batch), for the n = 6
-  // body alone it has no scratch and is 4.5 % faster (5.34 against 5.58 ms)
+  // body alone it has no scratch and is 4.5 % faster (5.34 against 5.58 ms).
+  // A 7-photon pair body in the same kernel takes 156 of a workgroup's 160 KB:
+  // the polarisations stay in registers there.
   // Bodies with the one-photon current cache (FP64 per point, 5..7 photons)
   // run 2 or 4 lanes per point and keep the cache in their wave's region of
   // qx_cache_mem.
@@ -80,6 +82,8 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
       pair64(procs.size(), 0);
   os << subset_header_text() << "\n";
   int pol_npart = 0, cache_w = 0, cache_w64 = 0;
+  bool pol_fits = true;
+  for (auto& p : procs) pol_fits = pol_fits && !(pair_eval(p.first, p.second) && pair_lds_doubles(p.first) > 0);
   for (size_t i = 0; i < procs.size(); ++i) {
     Dag d = graph_for(procs[i].first, procs[i].second, nullptr, nullptr);
     EmitStats st;
@@ -94,7 +98,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
     const int cw = body_cache_doubles(d, procs[i].second);
     cache[i] = cw > 0;
     cache_w = std::max(cache_w, cw);
-    pol[i] = !cache[i] && (procs[i].second.order & 8) && procs[i].second.block == 256 && procs[i].first.P >= 7;
+    pol[i] = pol_fits && !cache[i] && (procs[i].second.order & 8) && procs[i].second.block == 256 && procs[i].first.P >= 7;
     if (pol[i]) pol_npart = std::max(pol_npart, procs[i].first.npart);
     os << emit_body_function(d, procs[i].second, "qedx_body_" + std::to_string(i), &st, pol[i] != 0) << "\n";
     if (fix) {

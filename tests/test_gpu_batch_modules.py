@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2511_19456_amd import inputs
-from parity import per_point_ref
+from parity import check_fp64, per_point_ref
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +47,39 @@ def test_fp32c_batch_without_the_fp64_pass(tile):
             assert got[-1] == -7.0, n
             ok = kap <= 16.0
             assert ok.any() and np.abs(got[:-1][ok] / ref[ok] - 1.0).max() < 1e-4, (n, rep)
+
+
+@pytest.mark.parametrize("tile", [64, 256, 0])
+def test_default_and_explicit_shapes_in_one_batch(tile):
+    """FP64: processes without a kernel shape (pair bodies) beside such with one
+    (graph bodies: shared blocks, partition loops with and without the current
+    cache, the distributive rewrite), each n in both forms; at 6 photons out the
+    pair body alone fills the kernel's LDS."""
+    from paper_2511_19456_amd.qedx import BatchPlan, make_variant
+    explicit = {1: make_variant(block=256), 2: make_variant(rewrite=1, block=256), 3: make_variant(order=4),
+                4: make_variant(order=1288), 5: make_variant(order=520), 6: make_variant(order=8)}
+    spec = [(n, N, var) for n, N in ((1, 129), (2, 65), (3, 97), (4, 66), (5, 33), (6, 17)) for var in (None, explicit[n])]
+    segs, host = _segments(spec, "fp64")
+    plan = BatchPlan(segs, tile_points=tile)
+    for rep in range(2):
+        for h in host:
+            h[3].fill_(-7.0)
+        plan.launch()
+        torch.cuda.synchronize()
+        for (n, N, var), (_, mom, hel, out) in zip(spec, host):
+            ref, kap = per_point_ref(mom, n, hel)
+            got = out.cpu().numpy()
+            assert got[-1] == -7.0, n
+            check_fp64(got[:-1], ref, kap, f"n={n} {'explicit' if var else 'default'} shape, pass {rep}")
+
+
+@pytest.mark.parametrize("var", [dict(order=8), dict(rewrite=1, block=256)])
+def test_seven_photon_default_and_uncached_graph_body(var):
+    """Both 7-photon bodies that would keep something in LDS."""
+    from paper_2511_19456_amd.qedx import BatchPlan, make_variant
+    segs, host = _segments([(6, 33, None), (6, 65, make_variant(**var))], "fp64")
+    BatchPlan(segs, tile_points=64).launch()
+    torch.cuda.synchronize()
+    for n, mom, hel, out in host:
+        ref, kap = per_point_ref(mom, n, hel)
+        check_fp64(out.cpu().numpy()[:-1], ref, kap, f"n={n}")
