@@ -3,9 +3,9 @@
 //
 // Work is cut into tiles of 64 * chunk lanes of one segment, laid out by
 // decreasing cost per point (the static FLOP count of the kernels).  Each
-// wavefront takes its share of the tile space -- every W-th tile of W waves, or
-// (pair kernels) a contiguous range, cut on the host to equal cost -- and
-// evaluates it with the bodies of its segments' processes.  Grid size and tile length are
+// wavefront takes its share of the tile space, cut on the host to equal cost -- a
+// contiguous range of tiles (pair kernels), or some rounds of each segment (other
+// modules) -- and evaluates it with the bodies of its segments' processes.  Grid size and tile length are
 // picked by timing a few candidates once per plan signature; the choice is
 // kept in autotune.txt in the code-object cache directory.
 #include <hip/hip_runtime_api.h>
@@ -119,7 +119,7 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   os << "struct qedx_seg { const double* mom; const unsigned* hel; double* out; long long N; long long tile0; "
         "int proc; int shift; int shift64; long long list0; };\n";
   os << "extern \"C\" __global__ void __launch_bounds__(256)\n"
-        "qedx_batch(const qedx_seg* __restrict__ segs, int nseg, long long ntiles, int chunk"
+        "qedx_batch(const qedx_seg* __restrict__ segs, const int* __restrict__ share"
      << (fix ? ", double fix_kappa, unsigned* __restrict__ fix_cnt, unsigned* __restrict__ fix_list" : "")
      << ")\n{\n";
   std::string PT = "double";
@@ -129,15 +129,14 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
   if (cache_w > 0) os << "  __shared__ double2 qx_cache_mem[" << 2 * cache_w << "];\n";
   os << "  const int lane = threadIdx.x & 63;\n";
   os << "  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (threadIdx.x >> 6)));\n";
-  os << "  int s = 0;\n  for (long long t = w; t < ntiles; t += 4ll * gridDim.x) {\n";
-  os << "    while (s + 1 < nseg && segs[s + 1].tile0 <= t) ++s;\n";
-  os << "    const qedx_seg sg = segs[s];\n";
+  // the wave's share: entries (segment, first round of 64 lanes, rounds) in [share[w], share[w + 1])
+  os << "  const int last = share[w + 1];\n  for (int e = share[w]; e < last; e += 3) {\n";
+  os << "    const int s = share[e];\n    const qedx_seg sg = segs[s];\n";
   os << "    const int lp = lane >> sg.shift;\n";
   os << "    const unsigned sub = (unsigned)(lane & ((1 << sg.shift) - 1));\n";
-  os << "    const long long ppw = 64LL >> sg.shift;\n";
-  os << "    for (int c = 0; c < chunk; ++c) {\n";
-  os << "      const long long pt = (t - sg.tile0) * ppw * chunk + ppw * c + lp;\n";
-  os << "      if (pt - lp >= sg.N) break;\n";
+  os << "    const long long ppw = 64LL >> sg.shift, end = (long long)share[e + 1] + share[e + 2];\n";
+  os << "    for (long long t = share[e + 1]; t < end; ++t) {\n";
+  os << "      const long long pt = t * ppw + lp;\n";
   os << "      const long long ptc = pt < sg.N ? pt : sg.N - 1;\n";
   os << "      const unsigned hrt = sg.hel[ptc];\n";
   os << "      double r = 0.0;\n";
@@ -292,6 +291,11 @@ std::string pair_module_source() {
 // processes wait for.
 double tile_cost(double flops_per_point) { return flops_per_point + 1500.0; }
 
+// A lane's time with a point's share in the other modules' kernels: its FLOPs,
+// and 3500 more.  (FP32C, us per round of n = 1..6: 8.2, 11.6, 19, 35, 60, 271;
+// FLOPs per lane 484, 1332, 3972, 10492, 19932, 112748.)
+constexpr double kLaneCost = 3500.0;
+
 bool all_pair(const std::vector<std::pair<Process, Variant>>& pv) {
   for (auto& p : pv)
     if (p.first.n_in != 1 || !pair_eval(p.first, p.second)) return false;
@@ -338,6 +342,7 @@ struct qed_batch_plan {
   bool classes = false;   // ... one kernel per class of processes
   hipFunction_t f_class[kClasses] = {};
   long long cls_tile[kClasses + 1] = {};  // tiles of a class
+  int* d_share = nullptr;                 // other modules: the waves' shares (see their kernel)
   long long* d_cut = nullptr;             // first tile of every wave, and the end, of each kernel in turn
   int cut_at[kClasses] = {}, cut_groups[kClasses] = {};  // ... where a kernel's start, its workgroups
   int ncu = 256;
@@ -365,6 +370,7 @@ struct qed_batch_plan {
     }
     if (d_segs) (void)hipFree(d_segs);
     if (d_cut) (void)hipFree(d_cut);
+    if (d_share) (void)hipFree(d_share);
     if (d_fix) (void)hipFree(d_fix);
     if (mod) (void)hipModuleUnload(mod);
   }
@@ -385,7 +391,7 @@ static qed_status launch_eager(qed_batch_plan* b, hipStream_t s) {
   }
   const unsigned groups = (unsigned)b->grid;
   if (!b->f_fix) {
-    void* ba[] = {(void*)&b->d_segs, (void*)&b->nseg, (void*)&b->ntiles, (void*)&b->chunk};
+    void* ba[] = {(void*)&b->d_segs, (void*)&b->d_share};
     e = hipModuleLaunchKernel(b->f_batch, groups, 1, 1, 256, 1, 1, 0, s, ba, nullptr);
     if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("batch kernel: ") + hipGetErrorString(e));
     return QED_OK;
@@ -395,14 +401,50 @@ static qed_status launch_eager(qed_batch_plan* b, hipStream_t s) {
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("zero kernel: ") + hipGetErrorString(e));
   unsigned* cnt = b->d_fix;
   unsigned* list = b->d_fix + 64;
-  void* ba[] = {(void*)&b->d_segs,    (void*)&b->nseg, (void*)&b->ntiles, (void*)&b->chunk,
-                (void*)&b->fix_kappa, (void*)&cnt,     (void*)&list};
+  void* ba[] = {(void*)&b->d_segs, (void*)&b->d_share, (void*)&b->fix_kappa, (void*)&cnt, (void*)&list};
   e = hipModuleLaunchKernel(b->f_batch, groups, 1, 1, 256, 1, 1, 0, s, ba, nullptr);
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("batch kernel: ") + hipGetErrorString(e));
   void* fa[] = {(void*)&b->d_segs, (void*)&b->nseg, (void*)&cnt, (void*)&list};
   e = hipModuleLaunchKernel(b->f_fix, (unsigned)b->fix_grid, 1, 1, 256, 1, 1, 0, s, fa, nullptr);
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("fix-up kernel: ") + hipGetErrorString(e));
   return QED_OK;
+}
+
+// Adds `count` rounds of cost c each to waves of the given loads, one after the
+// other to the wave with the least: take[w] rounds to wave w.  A level is searched that
+// nearly all of them fill the waves to; the few left go to the lowest.
+static void fill_waves(std::vector<double>& load, long long count, double c, std::vector<int>& take) {
+  const size_t W = load.size();
+  take.assign(W, 0);
+  double lo = *std::min_element(load.begin(), load.end());
+  double hi = *std::max_element(load.begin(), load.end()) + c * ((double)count / (double)W + 1);
+  auto rounds = [&](double level, size_t w) { return level > load[w] ? (long long)((level - load[w]) / c) : 0LL; };
+  auto total = [&](double level) {
+    long long n = 0;
+    for (size_t w = 0; w < W; ++w) n += rounds(level, w);
+    return n;
+  };
+  while (hi - lo > 1e-3 * c && hi - lo > 1e-12 * hi) {
+    const double mid = 0.5 * (lo + hi);
+    (total(mid) <= count ? lo : hi) = mid;
+  }
+  long long left = count;
+  for (size_t w = 0; w < W; ++w) {
+    take[w] = (int)rounds(lo, w);
+    left -= take[w];
+    load[w] += take[w] * c;
+  }
+  std::vector<std::pair<double, size_t>> low(W);
+  while (left > 0) {
+    for (size_t w = 0; w < W; ++w) low[w] = {load[w], w};
+    const size_t n = (size_t)std::min<long long>(left, (long long)W);
+    std::nth_element(low.begin(), low.begin() + (n - 1), low.end());
+    for (size_t i = 0; i < n; ++i) {
+      ++take[low[i].second];
+      load[low[i].second] += c;
+    }
+    left -= (long long)n;
+  }
 }
 
 static qed_status layout_tiles(qed_batch_plan* b, const qed_segment* segs, const std::vector<int>& proc_of,
@@ -480,6 +522,37 @@ static qed_status layout_tiles(qed_batch_plan* b, const qed_segment* segs, const
     }
     hipError_t e = hipMemcpy(b->d_cut, cut.data(), sizeof(long long) * cut.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("tile ranges copy: ") + hipGetErrorString(e));
+  }
+  if (!b->pair && b->grid > 0) {
+    // every wave the same cost: it takes some rounds of each segment, so that
+    // errors of the cost model add up on none of them.  (Every W-th tile of W
+    // waves gives some a tile of the dearest process more than others and
+    // nothing for it: FP32C n = 1..6, 50001 points each, without the FP64 pass
+    // 667 us, from a counter that waves take tiles from 573, these shares 560.)
+    const size_t W = 4 * (size_t)b->grid;
+    std::vector<double> load(W, 0.0);
+    std::vector<int> take;
+    std::vector<std::vector<int>> of(W);
+    for (int k = 0; k < b->nseg; ++k) {
+      const DevSeg& d = b->host[k];
+      const long long per = 64LL >> d.shift, count = (d.N + per - 1) / per;
+      if (!count) continue;
+      fill_waves(load, count, cost[ord[k]] / (double)(1 << d.shift) + kLaneCost, take);
+      long long first = 0;
+      for (size_t w = 0; w < W; ++w)
+        if (take[w]) {
+          of[w].insert(of[w].end(), {k, (int)first, take[w]});
+          first += take[w];
+        }
+    }
+    std::vector<int> share(W + 1);
+    for (size_t w = 0; w < W; ++w) {
+      share[w] = (int)share.size();
+      share.insert(share.end(), of[w].begin(), of[w].end());
+    }
+    share[W] = (int)share.size();
+    hipError_t e = hipMemcpy(b->d_share, share.data(), sizeof(int) * share.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("wave shares copy: ") + hipGetErrorString(e));
   }
   hipError_t e = hipMemcpy(b->d_segs, b->host.data(), sizeof(DevSeg) * b->host.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return fail(QED_ERR_HIP, std::string("segment table copy: ") + hipGetErrorString(e));
@@ -577,6 +650,8 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   // four waves per workgroup, up to four workgroups per compute unit
   if (b->pair && hipMalloc((void**)&b->d_cut, sizeof(long long) * ((size_t)16 * ncu + kClasses)) != hipSuccess)
     return fail(QED_ERR_OOM, "tile range allocation failed");
+  if (!b->pair && hipMalloc((void**)&b->d_share, sizeof(int) * ((size_t)16 * ncu * (1 + 3 * (size_t)nseg) + 1)) != hipSuccess)
+    return fail(QED_ERR_OOM, "wave share allocation failed");
   // plan signature for the autotune cache
   long long total_lanes = 0;
   for (int i = 0; i < nseg; ++i) total_lanes += segs[i].N << b->shift[proc_of[i]];
@@ -586,11 +661,12 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   int grid = 0, chunk = 0;
   if (tile_points > 0) {
     chunk = tile_points / 64;
-    grid = ncu * 2;
+    grid = b->grid = ncu * 2;
     // one kernel per class where the batch fills the device several times over
     b->classes = b->pair && total_lanes >= (long long)ncu * 256 * 8;
   } else if (!tune_lookup(key.str(), grid, chunk)) {
-    // time candidates: workgroups per CU (x 4 waves) and tile length.  The
+    // time candidates: workgroups per CU (x 4 waves) and, for the pair module,
+    // tile length (the others' shares are cut to single rounds).  The
     // inputs may still be in flight on another stream: wait for the device.
     if ((st = chk(hipDeviceSynchronize(), "autotune sync"))) return st;
     hipEvent_t e0, e1;
@@ -605,7 +681,7 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
     std::vector<Candidate> cand;
     for (int wpc : {0, 1, 2, 4})  // 0: a kernel per class
       for (int ch : {1, 4, 16})
-        if (b->pair ? wpc <= 1 && ch <= 4 : wpc > 0) cand.push_back({wpc, ch, 1e30f});
+        if (b->pair ? wpc <= 1 && ch <= 4 : wpc > 0 && ch == 1) cand.push_back({wpc, ch, 1e30f});
     for (int pass = 0; pass < 2; ++pass)
       for (Candidate& c : cand) {
         b->classes = c.wpc == 0;
@@ -632,6 +708,8 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   if (!tile_points) b->classes = b->pair && grid == 0;
   b->grid = grid;
   b->chunk = chunk;
+  // (a grid from the cache of another device)
+  if (!b->pair) b->grid = std::max(1, std::min(b->grid, 4 * ncu));
   if ((st = layout_tiles(b.get(), segs, proc_of, cost))) return st;
   // capture: zero kernel, then the persistent kernel
   if ((st = chk(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture"))) return st;
