@@ -257,7 +257,7 @@ qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, int tile_poi
 qed_status qed_batch_launch(qed_batch_plan* plan, void* stream);
 qed_status qed_batch_plan_destroy(qed_batch_plan* plan);
 /* Tile layout chosen for a plan: tiles in the tile space, workgroups of the
- * persistent grid, 64-point chunks per tile. */
+ * persistent grid (of all kernels of a launch), 64-point chunks per tile. */
 qed_status qed_batch_info(const qed_batch_plan* plan, int64_t* ntiles, int* grid, int* chunk);
 /* Ahead-of-time build of the batch module for the per-point processes
  * n_list[0..count) with default kernel shapes, node-reduced (rewrite = 0) or

@@ -355,7 +355,7 @@ struct qed_batch_plan {
   int nseg = 0;
   long long ntiles = 0;
   int chunk = 1;
-  int grid = 0;  // workgroups of 256 threads
+  int grid = 0;  // workgroups of 256 threads (pair module: autotune's choice, 0 = a kernel per class)
   std::vector<int> shift, shift64;  // per distinct process: log2 of its bodies' lanes per point
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
@@ -740,7 +740,11 @@ extern "C" qed_status qed_batch_plan_destroy(qed_batch_plan* plan) {
 extern "C" qed_status qed_batch_info(const qed_batch_plan* plan, int64_t* ntiles, int* grid, int* chunk) {
   if (!plan) return fail(QED_ERR_INVALID_ARG, "plan is NULL");
   if (ntiles) *ntiles = plan->ntiles;
-  if (grid) *grid = plan->classes ? plan->ncu : plan->grid;
+  if (grid) {
+    // the workgroups that a launch starts, over all its kernels
+    *grid = plan->pair ? 0 : plan->grid;
+    for (int c = 0; plan->pair && c < (plan->classes ? kClasses : 1); ++c) *grid += plan->cut_groups[c];
+  }
   if (chunk) *chunk = plan->chunk;
   return QED_OK;
 }

@@ -83,3 +83,18 @@ def test_seven_photon_default_and_uncached_graph_body(var):
     for n, mom, hel, out in host:
         ref, kap = per_point_ref(mom, n, hel)
         check_fp64(out.cpu().numpy()[:-1], ref, kap, f"n={n}")
+
+
+@pytest.mark.parametrize("spec,tile", [([(1, 65)], 64), ([(6, 33), (2, 4097)], 64), ([(2, 300000), (5, 300000)], 64)])
+def test_batch_info_counts_the_workgroups_started(spec, tile):
+    """No more than four waves per workgroup have a tile to start with, and no
+    more workgroups than four per compute unit are started."""
+    from paper_2511_19456_amd.qedx import BatchPlan
+    segs, host = _segments([(n, N, None) for n, N in spec], "fp64")
+    info = BatchPlan(segs, tile_points=tile).info()
+    tiles = sum(-(-N // 32) for n, N in spec)     # two lanes per point
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert info["tiles"] == tiles
+    assert 1 <= info["grid"] <= min(-(-tiles // 4) + len(spec) - 1, 4 * ncu)
+    if tiles > 16 * ncu:                          # a full round of every kernel: one and two workgroups per unit
+        assert info["grid"] == 3 * ncu
