@@ -138,7 +138,9 @@ typedef struct {
   int32_t vgpr, agpr, sgpr, scratch_bytes, lds_bytes; /* from the code object */
   double create_ms_build, create_ms_reduce, create_ms_emit, create_ms_compile, create_ms_load;
   int32_t cache_hit;         /* 1 if the code object came from the cache */
-  char kernel_tag[160];      /* kernel shape: process, mode, precision, helicity coverage, schedule */
+  char kernel_tag[160];      /* kernel shape: process, precision, mode, and of graph kernels the helicity coverage
+                                and schedule, of the kernels with one current per photon subset "pair" (one
+                                configuration) or "coop" (helicity sum), lanes per point and block; _d1: rewrite */
   char code_hash[24];        /* hash of the eval kernel's source, flags and target (changes with the code) */
   char kernel_name[48];      /* symbol of the eval kernel, qedx_eval_[i<n_in>]n<n>_<sum|pp>_<fp64|fp32c>[_d1][_k<steps>] */
   int32_t n_in;              /* incoming photons (1 unless created by qed_process_create_crossed) */

@@ -451,6 +451,7 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
   info.fixup = v.fixup;
   info.fix_kappa = v.fixup ? fk : 0.0;
   proc = Process::make(n, nin);
+  const bool pair = pair_eval(proc, v), coop = coop_kernel(proc, v);
   try {
     double tb = 0, tr = 0;
     Dag un = build_unreduced(proc, v.enum_mask, v.split);
@@ -462,8 +463,6 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
     info.nodes_reduced = (int64_t)d.nodes.size();
     auto t0 = std::chrono::steady_clock::now();
     EmitStats st;
-    const bool pair = pair_eval(proc, v);
-    const bool coop = coop_kernel(proc, v);
     const std::string kname = eval_kernel_name(n, nin, mode, prec, v);
     src = pair ? emit_pair_kernel(proc, v, kname, &st)
                : coop ? emit_coop_kernel(proc, v, kname, &st) : emit_eval_kernel(d, v, kname, &st);
@@ -481,7 +480,11 @@ static qed_status build_source(int n, int nin, qed_hel_mode mode, qed_precision 
   info.n = n;
   info.mode = mode;
   info.precision = prec;
+  // the subset kernels take nothing of the graph kernel's shape but its name in the cache
   std::string tag = variant_tag(v, n, nin);
+  if (pair || coop)
+    tag = tag.substr(0, tag.find("_e")) + (pair ? "_pair_l" : "_coop_l") + std::to_string(info.lanes_per_point) + "_b" +
+          std::to_string(info.block) + (v.rewrite ? "_d" + std::to_string(v.rewrite) : "");
   snprintf(info.kernel_tag, sizeof info.kernel_tag, "%s", tag.c_str());
   snprintf(info.kernel_name, sizeof info.kernel_name, "%s", eval_kernel_name(n, nin, mode, prec, v).c_str());
   info.n_in = nin;
@@ -518,7 +521,7 @@ static qed_status prebuild(int nin, int n, qed_hel_mode mode, qed_precision prec
   KernelMeta meta;
   bool hit;
   double ms = 0, ms2 = 0;
-  s = get_code_object(info.kernel_tag, src, co, meta, hit, ms);
+  s = get_code_object(variant_tag(v, n, nin), src, co, meta, hit, ms);
   if (s) return s;
   if (with_aux && nin == 1) {
     std::string asrc;
@@ -561,7 +564,7 @@ static qed_status process_create(int nin, int n, qed_hel_mode mode, qed_precisio
   KernelMeta meta;
   bool hit = false;
   double ms = 0;
-  s = get_code_object(p->info.kernel_tag, p->eval_src, co, meta, hit, ms);
+  s = get_code_object(variant_tag(p->var, n, nin), p->eval_src, co, meta, hit, ms);
   if (s) return s;
   p->info.create_ms_compile = ms;
   p->info.cache_hit = hit ? 1 : 0;
