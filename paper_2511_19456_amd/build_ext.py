@@ -131,6 +131,12 @@ DEFAULT_KERNELS = [
     (4, 0, 0, dict(rewrite=1)), (4, 1, 0, dict(rewrite=1)), (5, 1, 0, dict(rewrite=1)), (6, 1, 0, dict(rewrite=1)),
     (1, 1, 0, dict(rewrite=1)), (2, 1, 0, dict(rewrite=1)), (3, 1, 0, dict(rewrite=1)),
     (3, 0, 1, dict(rewrite=1)), (5, 1, 1, dict(rewrite=1)),
+    # the graph kernels of FP64 processes, which a given shape selects (parity tests, bench legs)
+    (1, 0, 0, dict(block=256)), (2, 0, 0, dict(block=256)), (3, 0, 0, dict(block=256)), (4, 0, 0, dict(block=256)),
+    (3, 1, 0, dict(block=256)), (4, 1, 0, dict(block=256)), (5, 1, 0, dict(block=256)), (6, 1, 0, dict(block=256)),
+    (2, 0, 0, dict(rewrite=1, block=256)), (3, 0, 0, dict(rewrite=1, block=256)), (4, 0, 0, dict(rewrite=1, block=256)),
+    (4, 1, 0, dict(rewrite=1, block=256)), (5, 1, 0, dict(rewrite=1, block=256)), (6, 1, 0, dict(rewrite=1, block=256)),
+    (1, 0, 0, dict(n_in=3, block=256)), (1, 1, 0, dict(n_in=6, rewrite=1, block=256)),
     # the join of the distributive n = 3 helicity sum on the FP64 matrix cores (experiment)
     (3, 0, 0, dict(rewrite=1, order=128)),
     # kernel shapes the parity tests exercise
