@@ -39,7 +39,10 @@
 namespace qedx {
 
 // Second line of the sources compiled with FMAs formed within an expression
-// only: a process's eval kernel and the batch kernels give the same bits.
+// only: a process's eval kernel and the batch kernels of processes without a
+// given shape give the same bits.  (The pair bodies of the other modules, beside
+// graph bodies and in the FP64 pass of FP32C, are compiled with those and may
+// differ from them in the last bits.)
 constexpr const char* kContractOn = "// fp-contract: on\n";
 
 // Whether (process, variant) takes the pair body in FP64: its eval kernel if

@@ -98,3 +98,17 @@ def test_batch_info_counts_the_workgroups_started(spec, tile):
     assert 1 <= info["grid"] <= min(-(-tiles // 4) + len(spec) - 1, 4 * ncu)
     if tiles > 16 * ncu:                          # a full round of every kernel: one and two workgroups per unit
         assert info["grid"] == 3 * ncu
+
+
+@pytest.mark.parametrize("tile", [64, 1024])
+def test_default_fp64_batch_has_the_eval_kernels_bits(tile):
+    """Plans of processes without a kernel shape: their module and the eval
+    kernels form FMAs alike."""
+    from paper_2511_19456_amd.qedx import BatchPlan, make_variant
+    spec = [(n, N, None) for n, N in ((6, 65), (5, 257), (4, 1030), (3, 999), (2, 4097), (1, 333))]
+    spec += [(6, 33, make_variant(rewrite=1)), (3, 130, make_variant(rewrite=1))]
+    segs, host = _segments(spec, "fp64")
+    BatchPlan(segs, tile_points=tile).launch()
+    torch.cuda.synchronize()
+    for (p, mom, hel, out), (n, N, _) in zip(segs, spec):
+        assert torch.equal(out, p.eval(mom, hel)), (n, N)
