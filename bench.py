@@ -333,20 +333,25 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
     _leg(legs, "n3_sum_fp32c_2p20", want, n3_fp32c)
 
     def distributive(n, mode, rs, seed):
+        """The graph kernel with the distributive rewrite (a given shape: block =
+        256), beside the graph kernel of the node-reduced graph and against the
+        default kernel, which takes one current per photon subset."""
         def run():
             from paper_2511_19456_amd.qedx import make_variant
             N = 1 << 20
             u, h = inputs.rambo_inputs(seed, n, N, with_helicities=True)
             hd = torch.as_tensor(h.astype(np.int32), device=dev) if mode == "per_point" else None
             base = QedProcess(n, mode, "fp64")
-            dist = QedProcess(n, mode, "fp64", make_variant(rewrite=1))
+            node = QedProcess(n, mode, "fp64", make_variant(block=256))
+            dist = QedProcess(n, mode, "fp64", make_variant(rewrite=1, block=256))
             m = base.rambo(torch.as_tensor(u, device=dev), rs)
             o0 = torch.empty(N, dtype=torch.float64, device=dev)
             o1 = torch.empty(N, dtype=torch.float64, device=dev)
             ms0 = time_launches(lambda: base.eval(m, hd, out=o0), steps, 2)
+            ms_n = time_launches(lambda: node.eval(m, hd, out=o1), steps, 2)
             ms1 = time_launches(lambda: dist.eval(m, hd, out=o1), steps, 2)
-            r = rate(ms1, N, alg_flops(n, mode), FP64_VECTOR_PEAK_TFLOPS)
-            r.update({"ms_default_variant": ms0, "speedup_vs_default_variant": ms0 / ms1,
+            r = rate(ms1, N, dag_flops(n, mode, rewrite=1), FP64_VECTOR_PEAK_TFLOPS)
+            r.update({"ms_node_reduced": ms_n, "speedup_vs_node_reduced": ms_n / ms1, "ms_default_variant": ms0, "speedup_vs_default_variant": ms0 / ms1,
                       "rel_diff_vs_default_variant": rel_err_stats(o1, o0, per_point=(mode == "per_point")),
                       "kernel": dist.info()["kernel_name"]})
             return r
@@ -356,10 +361,10 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
     def mfma_join():
         """The distributive n = 3 helicity-sum graph with its joins (4 x 4
         complex dot blocks per photon partition) on the FP64 matrix cores,
-        against the kernel without joins, on the headline points."""
+        against the same graph's vector joins, on the headline points."""
         from paper_2511_19456_amd.qedx import make_variant
         N = ref_n3.numel()
-        vec = QedProcess(3, "sum", "fp64", make_variant(rewrite=1))
+        vec = QedProcess(3, "sum", "fp64", make_variant(rewrite=1, block=256))
         mat = QedProcess(3, "sum", "fp64", make_variant(rewrite=1, order=128))
         o0 = torch.empty(N, dtype=torch.float64, device=dev)
         o1 = torch.empty(N, dtype=torch.float64, device=dev)
@@ -506,7 +511,8 @@ def extra_legs(torch, inputs, QedProcess, dev, a, want, ref_n3, mom_n3):
         rows = []
         base = {}
         for k in ks + ["full"]:
-            v = None if k == "full" else make_variant(partial_steps=k, partial_seed=seed)
+            # (a given shape: the graph's kernel, not the one by photon subsets)
+            v = make_variant(block=256) if k == "full" else make_variant(partial_steps=k, partial_seed=seed)
             p = QedProcess(n, "per_point", "fp64", v)
             m = p.rambo(torch.as_tensor(u, device=dev), 15.0)
             row = {"k": k, "nodes": p.info()["nodes_reduced"], "scratch": p.info()["scratch_bytes"]}
