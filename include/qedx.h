@@ -4,8 +4,9 @@
  * electron line, all (n+1)! tree diagrams (Sec. III-A of the paper: the number
  * of orderings in which the photons bind to the electron).  The amplitude is
  * the paper's computation graph (Sec. II-B: base states U, vertices V,
- * propagators S1, joins S2, diagram Sum) after node reduction (App. C),
- * compiled into one straight-line GPU kernel per process variant.
+ * propagators S1, joins S2, diagram Sum), evaluated in FP64 with one current
+ * per photon subset (the distributive law of App. C taken to the end), otherwise
+ * after node reduction (App. C); one generated GPU kernel per process variant.
  *
  * Conventions shared by every entry point
  *  - Units hbar = c = 1, electron mass m = 1, metric (+,-,-,-).
@@ -109,9 +110,9 @@ typedef struct {
                            1 = node reduction followed by the distributive rewrite the paper
                            proposes (Sec. IV): sums over photon orderings are factored, so the
                            diagram sum becomes one join per photon partition and the currents
-                           one per photon subset.  Same result up to rounding.  The fused
-                           gradient (n <= 3) uses the node-reduced graph; the split gradient
-                           (n = 4) sweeps the process's own graph form. */
+                           one per photon subset.  Same result up to rounding.  It is the
+                           form of the graph kernels (FP32C, a given shape, FP64 sums of more
+                           than 5 photons); the gradient does not depend on it. */
   int32_t partial;      /* nonzero: instead of the full pipeline, the paper's unsplit graph
                            after only the first partial_steps single node reductions in the
                            random order seeded by partial_seed (0 steps = unreduced), emitted
@@ -194,7 +195,8 @@ qed_status qed_rambo(const qed_process* p, const double* uniforms, double sqrt_s
 /* log|M|^2 (SUM mode processes) and its gradient with respect to the RAMBO
  * uniforms: out_logm2 [N], out_grad [4(n+1)][N] (row = uniform index), both
  * float64 device buffers.  The gradient is the reverse sweep over the currents
- * of the photon subsets.  n <= 3: forward RAMBO, currents, reverse sweep and
+ * of the photon subsets (below sqrt_s = 1.1 by a kernel of its own, which keeps
+ * the digits that cancel near the threshold in the other).  n <= 3: forward RAMBO, currents, reverse sweep and
  * adjoint RAMBO in one kernel; no workspace (workspace may be NULL).  n = 4:
  * per chunk of points, RAMBO into the workspace, one kernel writing log|M|^2
  * and the momentum gradient, and the RAMBO adjoint.  The workspace is
@@ -217,7 +219,7 @@ qed_status qed_eval_grad_workspace_size(const qed_process* p, int64_t N, int64_t
  * harnesses that forbid allocation).  Same arguments, results and errors as
  * qed_eval_grad; the n = 4 split gradient runs its chunks through a fixed
  * scratch array the library holds on every GPU it runs on (256 MiB per
- * device, kept until the process ends), which caps a chunk at 2^16 points
+ * device, kept until the process ends), which caps a chunk at 599,186 points
  * at n = 4; any N runs, in ceil(N / chunk) passes.  A process whose 64-point
  * chunk would not fit is UNSUPPORTED.  The call allocates nothing and does
  * not synchronise.  All calls on one GPU share that GPU's scratch and the
@@ -244,8 +246,9 @@ typedef struct {
  * whose body splits a point over 2 or 4 lanes (0 = autotuned: a few
  * grid sizes and tile lengths are timed on the given buffers, which are
  * overwritten, after a device synchronisation; the choice is cached by plan
- * signature).  The plan copies the segment table and the waves' tile ranges
- * to the device and instantiates a HIP graph of one kernel node, or, for
+ * signature).  FP64 plans of processes without a given kernel shape hand whole
+ * tiles to the waves, the others rounds of 64 lanes whatever the tile.  The plan
+ * copies the segment table and the waves' shares to the device and instantiates a HIP graph of one kernel node, or, for
  * large FP64 batches of processes without a given kernel shape, one per class
  * of processes (n = 6; 4, 5; 1..3).  FP32C plans (per-point processes with
  * the FP64 fix-up) also allocate 4(64 + total points) bytes (a counter and a

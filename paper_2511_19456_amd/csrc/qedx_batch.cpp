@@ -53,9 +53,10 @@ Variant batch_variant(Variant v) {
 // FP32C per-point modules with the FP64 fix-up (every process of a batch
 // shares the precision, so the first one decides): the batch kernel lists
 // the points whose diagram sum cancels, per segment (a counter per segment,
-// the segment's region of the list), and qedx_batch_fix recomputes them with
-// FP64 bodies of the same graphs, one segment at a time per wave, so bodies
-// that split a point over several lanes run there too.
+// the segment's region of the list), and qedx_batch_fix recomputes them in FP64
+// (pair bodies, or of the same graphs where a kernel shape is given), one
+// segment at a time per wave, so bodies that split a point over several lanes
+// run there too.
 bool module_fixup(const std::vector<std::pair<Process, Variant>>& procs) {
   return !procs.empty() && procs[0].second.fixup != 0;
 }
@@ -209,7 +210,8 @@ std::string module_source(const std::vector<std::pair<Process, Variant>>& procs)
 
 // ---------------------------------------------------------------------------
 // Plans whose processes all take the pair kernels (FP64, no kernel shape asked
-// for) share one module for n = 1..6, so no plan waits for a compiler.  It
+// for) share one module for n = 1..6, so no plan waits for a compiler (an empty
+// code-object cache does, 19 s, where a module of n = 1 alone took 1).  It
 // holds a kernel for all processes, for batches too small to fill the device,
 // and one per class of processes with registers and LDS of that class: in the
 // common kernel the 7-photon body leaves every other one a single wave per
@@ -711,7 +713,7 @@ extern "C" qed_status qed_batch_plan_create(const qed_segment* segs, int nseg, i
   // (a grid from the cache of another device)
   if (!b->pair) b->grid = std::max(1, std::min(b->grid, 4 * ncu));
   if ((st = layout_tiles(b.get(), segs, proc_of, cost))) return st;
-  // capture: zero kernel, then the persistent kernel
+  // capture the kernels of a launch
   if ((st = chk(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture"))) return st;
   qed_status ls = launch_eager(b.get(), b->cap);
   hipError_t ce = hipStreamEndCapture(b->cap, &b->graph);

@@ -32,7 +32,7 @@ struct Variant {
   int partial_steps = 0;
   uint32_t partial_seed = 0;
   int subset = 0;       // 1: no kernel shape was asked for, so FP64 evaluation takes one current per photon
-                        // subset whatever the graph form; the fields above then shape FP32C and the gradient only
+                        // subset whatever the graph form; the fields above then shape FP32C only
   int fixup = 0;        // 1: FP32C per-point kernel flags ill-conditioned points for an FP64 pass
 };
 
